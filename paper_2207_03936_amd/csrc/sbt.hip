@@ -97,8 +97,11 @@ __global__ __launch_bounds__(B) void k_seed_follow(sbt_params P, HitsArgs H, Wor
     if (ws_evinfo(W)[e].st != 0) return;
     int hb, N;
     load_event<B>(P, H, e, S, &hb, &N);
-    stage_track<B, CAP, kCand>(P, event_view(W, e, hb, N), S, own_cap, true);
-    if (threadIdx.x == 0) ws_evinfo(W)[e].nfin = S.cnt[3];
+    const bool pos = stage_track<B, CAP, kCand>(P, event_view(W, e, hb, N), S, own_cap, true);
+    if (threadIdx.x == 0) {
+        ws_evinfo(W)[e].nfin = S.cnt[3];
+        ws_evinfo(W)[e].pos = pos ? 1 : 0;
+    }
 }
 
 // The paper's separate candidate pass (ablation): the pendulum start of every
@@ -121,7 +124,8 @@ __global__ __launch_bounds__(B) void k_weak_filter(sbt_params P, HitsArgs H, Wor
     if (ws_evinfo(W)[e].st != 0) return;
     const int hb = H.eo[e];
     const Ev v = event_view(W, e, hb, H.eo[e + 1] - hb);
-    stage_filter<B>(P, v, ws_evinfo(W)[e].nfin, v.own());
+    if (ws_evinfo(W)[e].pos) stage_filter_pos<B>(P, v, ws_evinfo(W)[e].nfin);
+    else stage_filter<B>(P, v, ws_evinfo(W)[e].nfin, v.own());
 }
 
 template <int B>
@@ -134,7 +138,9 @@ __global__ __launch_bounds__(B) void k_compact(HitsArgs H, Work W, int lds_bytes
         return;
     }
     const int hb = H.eo[e];
-    stage_compact<B>(event_view(W, e, hb, H.eo[e + 1] - hb), scan, lds_bytes);
+    const Ev v = event_view(W, e, hb, H.eo[e + 1] - hb);
+    if (ws_evinfo(W)[e].pos) stage_compact<B, true>(v, scan, lds_bytes);
+    else stage_compact<B, false>(v, scan, lds_bytes);
 }
 
 // batched form ----------------------------------------------------------------

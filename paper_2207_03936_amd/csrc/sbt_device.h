@@ -68,7 +68,8 @@ struct EvInfo {
     int32_t st;         // SBT_EV_* status
     int32_t nfin;       // final records (plain form)
     int32_t out_t;      // first output track position (batch scan)
-    int32_t pad[2];
+    int32_t pos;        // 1: the LDS form tracked it (plain form)
+    int32_t pad;
 };
 
 // record flags
@@ -162,23 +163,24 @@ __device__ __forceinline__ uint16_t phi16(float x, float y)
     const float half_pi = 0x1.921fb6p+0f;
     const float pi = 0x1.921fb6p+1f;
     const float scale = 0x1.45f306p+13f;   // 32768 / pi
-    float a = x < 0.0f ? -x : x;
-    float b = y < 0.0f ? -y : y;
-    if (a == 0.0f && b == 0.0f) return 0;
-    float mn = a < b ? a : b;
+    // |x| and |y| differ from the comparison form in the sign of a zero only,
+    // which never reaches the result
+    const float a = __builtin_fabsf(x), b = __builtin_fabsf(y);
+    const float mn = a < b ? a : b;
     float mx = a < b ? b : a;
-    float r = mn / mx;
-    float s = r * r;
+    mx = mx == 0.0f ? 1.0f : mx;   // (0, 0) has angle 0
+    const float r = mn / mx;
+    const float s = r * r;
     float p = c4;
     p = p * s + c3;
     p = p * s + c2;
     p = p * s + c1;
     p = p * s + c0;
     float at = r * p;
-    if (b > a) at = half_pi - at;
-    if (x < 0.0f) at = pi - at;
-    if (y < 0.0f) at = -at;
-    int q = (int)__builtin_rintf(at * scale);
+    at = b > a ? half_pi - at : at;
+    at = x < 0.0f ? pi - at : at;
+    at = y < 0.0f ? -at : at;
+    const int q = (int)__builtin_rintf(at * scale);
     return (uint16_t)(q & 0xFFFF);
 }
 
@@ -240,15 +242,16 @@ __device__ __forceinline__ void ev_lds_sync()
 // every module step, so values derived from them are recomputed per step
 // instead of being hoisted out of the event and step loops, where dozens of
 // them would stay live in scalar registers (and spill) for the whole kernel.
-// The "+s" operand must reach the asm in a scalar register: where a change
-// elsewhere in a kernel leaves the compiler holding it in a vector register,
-// compilation stops with an illegal VGPR-to-SGPR copy (a readfirstlane on
-// the input resolves it, at the price of a different register allocation).
+// Where a kernel's control flow leaves the compiler holding the value in a
+// vector register, the readfirstlane brings it back to a scalar one, as the
+// asm operand needs; elsewhere it costs nothing.
 template <class T>
 __device__ __forceinline__ T opq(T v)
 {
-    asm volatile("" : "+s"(v));
-    return v;
+    static_assert(sizeof(T) == 4, "one scalar register");
+    int x = uni(__builtin_bit_cast(int, v));
+    asm volatile("" : "+s"(x));
+    return __builtin_bit_cast(T, x);
 }
 
 // A workspace pointer hidden from the optimiser (see opq) that stays known
@@ -256,7 +259,8 @@ __device__ __forceinline__ T opq(T v)
 typedef __attribute__((address_space(1))) char gchar;
 __device__ __forceinline__ char *opq_global(char *p)
 {
-    uint64_t v = reinterpret_cast<uint64_t>(p);
+    const uint64_t a = reinterpret_cast<uint64_t>(p);
+    uint64_t v = ((uint64_t)(uint32_t)uni((int)(uint32_t)(a >> 32)) << 32) | (uint32_t)uni((int)(uint32_t)a);
     asm volatile("" : "+s"(v));
     return (char *)(gchar *)v;
 }
@@ -280,6 +284,17 @@ __device__ __forceinline__ Prm fresh(const sbt_params &P)
     p.Sf = __int_as_float(opq(__float_as_int(P.max_scatter_forwarding)));
     p.X = __int_as_float(opq(__float_as_int(P.max_tracklet_chi2)));
     return p;
+}
+
+// The parameter block of the running kernel (its first argument), by an
+// address hidden from the optimiser: each use is a scalar load where it
+// stands, instead of registers held (and spilled) through the whole kernel.
+typedef __attribute__((address_space(4))) const sbt_params cparams;
+__device__ __forceinline__ const sbt_params &kernel_params()
+{
+    uint64_t a = reinterpret_cast<uint64_t>(__builtin_amdgcn_kernarg_segment_ptr());
+    asm volatile("" : "+s"(a));
+    return *(const sbt_params *)reinterpret_cast<cparams *>(a);
 }
 
 __device__ __forceinline__ int kmod(const Prm &p, int t) { return p.rev ? p.M - 1 - t : t; }
@@ -417,7 +432,7 @@ __device__ __forceinline__ int block_count2(bool pa, bool pb, int *s_w, int phas
 
 // in-place exclusive scan of a[0..n) in LDS
 template <int B>
-__device__ void block_scan_inplace(int *a, int n, int *s_w)
+__device__ __forceinline__ void block_scan_inplace(int *a, int n, int *s_w)
 {
     const int chunk = (n + B - 1) / B;
     const int beg = tid<B>() * chunk;
@@ -449,33 +464,27 @@ __device__ __forceinline__ int lane_xor(int v, int m)
 //   ring   4 slots x CAP sorted hits (16 B each): traversal index u in slot
 //          u mod 4; module t+1 is filled into the slot of t-3 while t is
 //          being resolved
-//   tab    coarse phi index of each slot: first position whose phi16 high
-//          byte is >= b, b = 0..256
+//   seeds  the seeds of a step, three words each (CAP entries): window
+//          positions of the three hits, best position of the first following
+//          search and its scatter
+//   claim  claim words (4 B) of five modules, traversal index u in slot
+//          u mod 5, by window position
 //   freel  unflagged positions of the seeding stage's doublet module
-//   freem  unflagged positions of the middle module
-//   frank  unflagged positions before each doublet-module position
-//   al0/1  active-track lists (CAP entries; more sends the event to memory)
-//   res    per active slot: the search result (best hit id | window position
-//          << 16, scatter) and the claim set's inputs (key, seed hits)
-//   cfree  unflagged-position bits of the seeding stage's third module
-//   lclaim claim words of the module being searched by the following
-//          stage, by window position (the claims on seed hits stay in memory)
-//   own    hit-flag bitmap of the event when N <= own_cap
+//   tab    coarse phi index of each slot: first position whose phi16 is in
+//          bin b or above it
+//   own    hit flags of the event, one bit per sorted position, when
+//          N <= own_cap (two words of slack behind it)
 extern __shared__ __align__(16) char g_lds[];
 
-constexpr int kTab = 257;
+constexpr int kTab = 256;   // bins of the coarse phi index, at most
 constexpr int kSlots = 4;   // ring slots: traversal indices t-2 .. t+1
+constexpr int kClaimSlots = 5;   // claim slots: traversal indices t-4 .. t
 __host__ __device__ constexpr uint32_t a16(uint32_t v) { return (v + 15u) & ~15u; }
-__host__ __device__ constexpr uint32_t lay_tab(int cap) { return 16u * kSlots * (uint32_t)cap; }
-__host__ __device__ constexpr uint32_t lay_freel(int cap) { return a16(lay_tab(cap) + 2u * kSlots * kTab); }
-__host__ __device__ constexpr uint32_t lay_freem(int cap) { return lay_freel(cap) + a16(2u * cap); }
-__host__ __device__ constexpr uint32_t lay_frank(int cap) { return lay_freem(cap) + a16(2u * cap); }
-__host__ __device__ constexpr uint32_t lay_al0(int cap) { return lay_frank(cap) + a16(2u * cap); }
-__host__ __device__ constexpr uint32_t lay_al1(int cap) { return lay_al0(cap) + a16(2u * cap); }
-__host__ __device__ constexpr uint32_t lay_res(int cap) { return lay_al1(cap) + a16(2u * cap); }
-__host__ __device__ constexpr uint32_t lay_cfree(int cap) { return lay_res(cap) + 16u * cap; }
-__host__ __device__ constexpr uint32_t lay_lclaim(int cap) { return lay_cfree(cap) + a16(8u * (uint32_t)((cap + 63) / 64)); }
-__host__ __device__ constexpr uint32_t lay_own(int cap) { return lay_lclaim(cap) + 8u * (uint32_t)cap; }
+__host__ __device__ constexpr uint32_t lay_seeds(int cap) { return 16u * kSlots * (uint32_t)cap; }
+__host__ __device__ constexpr uint32_t lay_claim(int cap) { return lay_seeds(cap) + 12u * (uint32_t)cap; }
+__host__ __device__ constexpr uint32_t lay_freel(int cap) { return lay_claim(cap) + 4u * kClaimSlots * (uint32_t)cap; }
+__host__ __device__ constexpr uint32_t lay_tab(int cap) { return lay_freel(cap) + a16(2u * (uint32_t)cap); }
+__host__ __device__ constexpr uint32_t lay_own(int cap) { return lay_tab(cap) + 2u * kSlots * kTab; }
 
 // sort bins: 1024 in total, a power of two per module
 constexpr int kSortBins = 1024;
@@ -484,7 +493,7 @@ __host__ __device__ constexpr uint32_t lds_sort_head() { return a16((2u * kSortB
 __host__ __device__ inline uint32_t lds_bytes(int cap, int own_cap)
 {
     const uint32_t sort = lds_sort_head() + 4u * 1024u;   // keys of 1,024 hits at least
-    const uint32_t track = cap > 0 ? lay_own(cap) + a16(4u * (uint32_t)((own_cap + 31) / 32)) : 0u;
+    const uint32_t track = cap > 0 ? lay_own(cap) + a16(4u * (uint32_t)((own_cap + 31) / 32) + 8u) : 0u;
     return sort > track ? sort : track;
 }
 __host__ __device__ inline int lds_sortcap(int cap, int own_cap)
@@ -505,28 +514,27 @@ struct Lay {
     {
         return reinterpret_cast<Hit16 *>(g_lds + lo) + s * CAP;
     }
+    // word w of every seed: seeds(lo, w)[l]
+    static __device__ __forceinline__ uint32_t *seeds(uint32_t lo, int w)
+    {
+        return reinterpret_cast<uint32_t *>(g_lds + lo + lay_seeds(CAP)) + w * CAP;
+    }
+    static __device__ __forceinline__ uint32_t *claim(uint32_t lo) { return reinterpret_cast<uint32_t *>(g_lds + lo + lay_claim(CAP)); }
+    static __device__ __forceinline__ uint16_t *freel(uint32_t lo) { return reinterpret_cast<uint16_t *>(g_lds + lo + lay_freel(CAP)); }
     static __device__ __forceinline__ uint16_t *tab(uint32_t lo, int s)
     {
         return reinterpret_cast<uint16_t *>(g_lds + lo + lay_tab(CAP)) + s * kTab;
     }
-    static __device__ __forceinline__ uint16_t *freel(uint32_t lo) { return reinterpret_cast<uint16_t *>(g_lds + lo + lay_freel(CAP)); }
-    static __device__ __forceinline__ uint16_t *freem(uint32_t lo) { return reinterpret_cast<uint16_t *>(g_lds + lo + lay_freem(CAP)); }
-    static __device__ __forceinline__ uint16_t *frank(uint32_t lo) { return reinterpret_cast<uint16_t *>(g_lds + lo + lay_frank(CAP)); }
-    static __device__ __forceinline__ uint16_t *al(uint32_t lo, int i)
-    {
-        return reinterpret_cast<uint16_t *>(g_lds + lo + (i ? lay_al1(CAP) : lay_al0(CAP)));
-    }
-    static __device__ __forceinline__ uint4 *res(uint32_t lo) { return reinterpret_cast<uint4 *>(g_lds + lo + lay_res(CAP)); }
     static __device__ __forceinline__ uint32_t *own(uint32_t lo) { return reinterpret_cast<uint32_t *>(g_lds + lo + lay_own(CAP)); }
-    static __device__ __forceinline__ unsigned long long *cfree(uint32_t lo)
-    {
-        return reinterpret_cast<unsigned long long *>(g_lds + lo + lay_cfree(CAP));
-    }
-    static __device__ __forceinline__ unsigned long long *lclaim(uint32_t lo)
-    {
-        return reinterpret_cast<unsigned long long *>(g_lds + lo + lay_lclaim(CAP));
-    }
 };
+
+// Forming tracks of the LDS form are held in registers, one per lane and
+// set; as many sets as the slots have hits per lane, at most four.
+template <int B, int CAP>
+__host__ __device__ constexpr int track_sets()
+{
+    return CAP <= B ? 1 : (CAP + B - 1) / B > 4 ? 4 : (CAP + B - 1) / B;
+}
 
 // static LDS shared by the stages of one event
 template <int B>
@@ -536,10 +544,13 @@ struct Shared {
     int status;
     int e;
     int maxmod;          // hits of the event's largest module
-    int ovf;             // an LDS list overflowed
     int scan[2 * (B / 64)];
-    int slot_n[kSlots];  // hits of the module held by each ring slot
-    uint8_t mtab[(SBT_MAX_EVENT_HITS + 64) / 64];   // module of every 64th hit (sort)
+    int ctl[4];          // LDS form: seeds of a step by its parity (0, 1), a tie of claims, final records
+    int nfree[2][2][B / 64];   // free track slots of each wave, by step parity: sets 0 | 1 << 16, sets 2 | 3 << 16
+    union alignas(16) {
+        uint8_t mtab[(SBT_MAX_EVENT_HITS + 64) / 64];   // module of every 64th hit (sort)
+        int4 mt[SBT_MAX_MODULES];   // by traversal index: first sorted position, hits, nominal z (LDS form)
+    };
 };
 
 // Events of 64 lanes run one per wave, up to this many in a workgroup; each
@@ -569,6 +580,8 @@ struct Ev {
         return reinterpret_cast<T *>(base + (uint64_t)H * off + (uint64_t)(uint32_t)hb * elem);
     }
     __device__ __forceinline__ Rec *rec() const { return arr<Rec>(kOffRec, 32); }
+    __device__ __forceinline__ uint4 *fin() const { return reinterpret_cast<uint4 *>(rec()); }   // final records of the LDS form
+    __device__ __forceinline__ uint16_t *sid() const { return list(kListFRank); }                // its ids by sorted position
     __device__ __forceinline__ Hit16 *hs() const { return arr<Hit16>(kOffHs, 16); }
     __device__ __forceinline__ RecAux *aux() const { return arr<RecAux>(kOffAux, 16); }
     __device__ __forceinline__ unsigned long long *claim() const { return arr<unsigned long long>(kOffClaim, 8); }
@@ -615,7 +628,7 @@ __device__ __forceinline__ Ev fresh(const Ev &v)
 // ---------------------------------------------------------------- validation
 // Loads the event-local module offsets into LDS and checks the offsets.
 template <int B>
-__device__ int load_event(const sbt_params &P, const HitsArgs &H, int e, Shared<B> &S,
+__device__ __forceinline__ int load_event(const sbt_params &P, const HitsArgs &H, int e, Shared<B> &S,
                           int *hb_out, int *n_out)
 {
     const int M = P.n_modules;
@@ -713,7 +726,7 @@ __device__ __forceinline__ int sort_bin(const int *mo, const uint8_t *mtab, int 
 constexpr int kSortChunk = 8;
 
 template <int B>
-__device__ void stage_sort(const sbt_params &PP, const HitsArgs &H, const Ev &v0, Shared<B> &S, int sortcap)
+__device__ __forceinline__ void stage_sort(const sbt_params &PP, const HitsArgs &H, const Ev &v0, Shared<B> &S, int sortcap)
 {
     const Ev v = fresh(v0);
     const int M = fresh(PP).M, N = v.N;
@@ -804,13 +817,13 @@ __device__ void stage_sort(const sbt_params &PP, const HitsArgs &H, const Ev &v0
 
 // ---------------------------------------------------------------- module windows
 // An event whose modules all fit the LDS slots (and whose hit flags fit the
-// LDS bitmap) runs the LDS instantiation of the tracking stages: traversal
-// index u lives in ring slot u mod 4 and every window access is an LDS access.
-// Any other event runs the memory instantiation, which reads the sorted
-// hits in memory directly.  Both compute the same thing.
+// LDS bitmap) runs the LDS form of the tracking stages: traversal index u
+// lives in ring slot u mod 4 and every window access is an LDS access.  Any
+// other event runs the memory form, which reads the sorted hits in memory
+// directly.  Both compute the same thing.  The LDS form names a hit by its
+// sorted position, the memory form by its id.
 struct Win {
     const Hit16 *h;
-    const uint16_t *tab;   // coarse index (LDS instantiation)
     int n;
 };
 
@@ -820,15 +833,8 @@ __device__ __forceinline__ uint16_t win_q(const Win &w, int p) { return (uint16_
 __device__ __forceinline__ uint16_t win_id(const Win &w, int p) { return (uint16_t)(at(w.h, p).qid >> 16); }
 
 // first position of the window whose phi16 is >= v
-template <bool kLds>
 __device__ __forceinline__ int win_lower_bound(const Win &w, uint16_t v)
 {
-    if (kLds) {
-        int p = at(w.tab, v >> 8);
-        const int end = at(w.tab, (v >> 8) + 1);
-        while (p < end && win_q(w, p) < v) ++p;
-        return p;
-    }
     int lo = 0, hi = w.n;
     while (lo < hi) {
         int mid = (lo + hi) >> 1;
@@ -837,67 +843,30 @@ __device__ __forceinline__ int win_lower_bound(const Win &w, uint16_t v)
     return lo;
 }
 
-template <int B, bool kLds, int CAP>
+template <int B>
 __device__ __forceinline__ Win window(const Prm &P, const Shared<B> &S, const Ev &v, int u)
 {
     Win w;
-    if (kLds) {
-        const int s = u % kSlots;
-        w.n = uni(S.slot_n[s]);
-        w.h = Lay<CAP>::ring(v.lo, s);
-        w.tab = Lay<CAP>::tab(v.lo, s);
-    } else {
-        const int k = kmod(P, u);
-        const int g0 = uni(S.mo[k]);
-        w.n = uni(S.mo[k + 1]) - g0;
-        w.h = v.hs() + g0;
-        w.tab = nullptr;
-    }
+    const int k = kmod(P, u);
+    const int g0 = uni(S.mo[k]);
+    w.n = uni(S.mo[k + 1]) - g0;
+    w.h = v.hs() + g0;
     return w;
 }
 
-// coarse-index entries owned by position i > 0 of a slot whose phi16 is q
-// (qp: phi16 of position i-1): every high byte b with high(qp) < b <=
-// high(q) starts at i.  The entries up to the first hit's high byte (0) and
-// above the last hit's (n) are written by all lanes together.
-__device__ __forceinline__ void tab_fill(uint16_t *tab, int i, uint16_t q, uint16_t qp)
-{
-    if (i == 0) return;
-    for (int b = (qp >> 8) + 1; b <= (q >> 8); ++b) tab[b] = (uint16_t)i;
-}
-
-// Copies the sorted hits of traversal index u into its ring slot and builds
-// the slot's coarse index, on lanes [l0, B) of the workgroup.
-template <int B, int CAP>
-__device__ __forceinline__ void ring_fill(const Prm &P, const Ev &v, int u, Shared<B> &S, int l0)
-{
-    const int lane = (int)tid<B>() - l0, nl = B - l0;
-    if (lane < 0) return;
-    const int k = kmod(P, u);
-    const int g = uni(S.mo[k]), n = uni(S.mo[k + 1]) - g;
-    const int s = u % kSlots;
-    if (lane == 0) S.slot_n[s] = n;
-    Hit16 *ring = Lay<CAP>::ring(v.lo, s);
-    uint16_t *tab = Lay<CAP>::tab(v.lo, s);
-    const Hit16 *src = v.hs() + g;
-    // n == 0: every entry is 0
-    int hi_first = kTab, hi_last = kTab;
-    if (n > 0) {
-        hi_first = q_of(at(src, 0)) >> 8;
-        hi_last = q_of(at(src, n - 1)) >> 8;
-    }
-    for (int b = lane; b < kTab; b += nl) {
-        if (b <= hi_first) tab[b] = 0;
-        else if (b > hi_last) tab[b] = (uint16_t)n;
-    }
-    for (int i = lane; i < n; i += nl) {
-        const Hit16 h = at(src, i);
-        ring[i] = h;
-        tab_fill(tab, i, q_of(h), i > 0 ? q_of(at(src, i - 1)) : (uint16_t)0);
-    }
-}
-
 // ---------------------------------------------------------------- seeding
+// Tracklet fit of a seed, hits in traversal order (Section 3, "Tracklet
+// filter"): chi2 = ((v.x)^2 + (v.y)^2) / (v.v) with v = (z2-z1, z0-z2, z1-z0)
+// orthogonal to (1,1,1) and to z
+__device__ __forceinline__ float seed_chi2(const Hit16 &h0, const Hit16 &h1, const Hit16 &h2)
+{
+    const float v0 = h2.z - h1.z, v1 = h0.z - h2.z, v2 = h1.z - h0.z;
+    const float ssx = ((v0 * h0.x) + (v1 * h1.x)) + (v2 * h2.x);
+    const float ssy = ((v0 * h0.y) + (v1 * h1.y)) + (v2 * h2.y);
+    const float n2 = ((v0 * v0) + (v1 * v1)) + (v2 * v2);
+    return ((ssx * ssx) + (ssy * ssy)) / n2;
+}
+
 // The pendulum search visits the doublet module's phi-sorted positions in
 // the order s0, s0-1, s0+1, s0-2, s0+2, ... (wrapping, at most n visits) and
 // keeps the first K unflagged ones.  Here the unflagged positions are first
@@ -986,15 +955,755 @@ __device__ __forceinline__ int pendulum_quad(const uint16_t *F, int nf, int j, i
     return pos;
 }
 
+
+// ================================================================ LDS form
+// One step costs two barriers.  R(t): every forming track tests the claims of
+// its search into t and extends, waits or ends; the next module enters the
+// ring.  S(t): the seeds of t and their first search, and the kept tracks'
+// searches, all into t+1.  What bounds it is the dependent chain of a step
+// (LDS round trips, correctly rounded divisions, window walks), run 24 times
+// per event, and the instructions issued for it, so
+//   - a forming track stays in the registers of one lane from its seed to its
+//     end, and its step touches no memory but the previous-hit link it leaves
+//     behind; new seeds go to the lowest free lanes, so that few waves carry
+//     tracks and the others seed;
+//   - hits are named by sorted position, so the flags of a module are a run of
+//     bits and every wave that seeds takes the unflagged positions from a few
+//     words by itself, without a barrier;
+//   - the claims on a bare seed's hits are LDS words like those on the best
+//     hits (five modules of them), and the sorted hits of the module after
+//     the next are in registers a step before they are needed.
+// Measured against the form before it (tracks as 32-byte records in memory,
+// hits named by id, four barriers a step; microseconds a call): one event of
+// 500 hits 121 -> 81, one mu = 7.6 event 181 -> 124, mu = 7.6 x 1,000 452 ->
+// 350, mu in U{1..25} x 10,000 5,796 -> 4,142.
+
+struct LWin {
+    const Hit16 *h;
+    const uint16_t *tab;
+    int n, sh;      // hits; phi16 >> sh is the coarse index bin
+};
+
+// about one bin per hit: 32 to kTab bins
+__device__ __forceinline__ int tab_shift(int n) { return n > 192 ? 8 : n > 96 ? 9 : n > 48 ? 10 : 11; }
+
+template <int CAP>
+__device__ __forceinline__ LWin lds_window(uint32_t lo, int u, int n)
+{
+    LWin w;
+    w.h = Lay<CAP>::ring(lo, u & (kSlots - 1));
+    w.tab = Lay<CAP>::tab(lo, u & (kSlots - 1));
+    w.n = n;
+    w.sh = tab_shift(n);
+    return w;
+}
+
+// forming track: its last two hits, the seed's hits and the last one by
+// sorted position, and the result of its search
+struct Trk {
+    float xa, ya, za, xb, yb, zb;
+    uint32_t k0;     // key | h0 << 16
+    uint32_t h12;    // h1 | h2 << 16
+    uint32_t lst;    // last | hits << 16 | traversal index of the last << 24; 0: no track
+    uint32_t pb;     // window position of the best hit, or kNoPos
+    float bsc;       // its scatter
+};
+constexpr uint32_t kNoPos = 0xFFFFu;
+
+// final record of the LDS form: key | h0 << 16, h1 | h2 << 16, last | hits << 16
+typedef uint4 Fin;
+
+// Claim word of the LDS form: 63 - stage above the leading 26 bits of the
+// score.  As in claim_key, a word left from an earlier stage is larger than
+// any of a later one.  Of two claims of one stage that agree in those bits on
+// one word the second meets its own value there; the resolution then settles
+// that stage over 64-bit words in memory (claim_key).
+__device__ __forceinline__ uint32_t claim32(float score, int stage)
+{
+    return ((uint32_t)(63 - stage) << 26) | (__float_as_uint(score) >> 5);
+}
+
+// Walks the window [lo, lo + span] of phi16 from the start of lo's bin on
+// `stride` lanes (this one the k-th) and calls hit(h, p, in) for the positions
+// this lane meets, in or out of the window: positions of the bin below lo
+// come first (their distance to lo is within a bin of a full turn), then the
+// window, then one beyond it.  A position may be met twice where a stride
+// closes the circle; the callers take minima.  The lanes of a wave walk
+// together until the last one is done, with masks for branches: what a walk
+// costs is the instructions of its longest window.
+template <class F>
+__device__ __forceinline__ void walk(const LWin &w, uint32_t lo, uint32_t span, int k, int stride, F &&hit)
+{
+    uint32_t p = at(w.tab, lo >> w.sh) + (uint32_t)k;
+    p = min(p, p - (uint32_t)w.n);   // p - n is huge while p < n
+    unsigned long long live = __ballot(k < w.n);
+    p = k < w.n ? p : 0u;
+    const uint32_t below = 0x10000u - (1u << w.sh);
+    for (int j = 0; j < w.n; j += stride) {
+        const Hit16 h = at(w.h, p);
+        const uint32_t d = (h.qid - lo) & 0xFFFFu;
+        const unsigned long long in = __ballot(d <= span);
+        hit(h, (int)p, __builtin_amdgcn_inverse_ballot_w64(in & live));
+        live &= in | __ballot(d >= below);
+        if (live == 0ull) break;
+        const uint32_t x = p + (uint32_t)stride;   // within the slots' capacity in any case
+        p = min(x, x - (uint32_t)w.n);
+    }
+}
+
+// Search of a track into the window: best hit by (scatter, id) under Sf, as
+// one word that orders like the pair, and its position.
+__device__ __forceinline__ void follow_walk(const LWin &w, float xb, float yb, float zb, float tx, float ty, float Zn,
+                                            int Wf, float Sf, int k, int stride, unsigned long long &bk, uint32_t &bp)
+{
+    const float dzc = Zn - zb;
+    const uint32_t lo = (uint32_t)(phi16(xb + tx * dzc, yb + ty * dzc) - Wf) & 0xFFFFu;
+    walk(w, lo, 2u * (uint32_t)Wf, k, stride, [&](const Hit16 &h, int p, bool in) {
+        const float dz = h.z - zb;
+        const float dx = (xb + tx * dz) - h.x;
+        const float dy = (yb + ty * dz) - h.y;
+        const float sc = (dx * dx) + (dy * dy);
+        const unsigned long long key = ((unsigned long long)__float_as_uint(sc) << 32) | (h.qid >> 16);
+        const bool better = in && sc < Sf && key < bk;
+        bk = better ? key : bk;
+        bp = better ? (uint32_t)p : bp;
+    });
+}
+
+// Scalars of step t, by module: index i is traversal index t - 4 + i.
+struct Step {
+    int t;
+    int g[7], n[7];      // first sorted position, hits
+    int c[5];            // claim slot offsets (index 5, t + 1, shares that of t - 4)
+    float Zc, Zn, Zx;    // nominal z of t, t + 1 and t + 2
+};
+
+// position of set bit r of m
+__device__ __forceinline__ int nth_set(unsigned long long m, int r)
+{
+    uint32_t w = (uint32_t)m;
+    int base = 0;
+    int c = __popc(w);
+    if (r >= c) { r -= c; w = (uint32_t)(m >> 32); base = 32; }
+#pragma unroll
+    for (int s = 16; s > 0; s >>= 1) {
+        c = __popc(w & ((1u << s) - 1u));
+        if (r >= c) { r -= c; w >>= s; base += s; }
+    }
+    return base;
+}
+
+// unflagged positions [64 w, 64 w + 64) of a module of n hits whose first
+// sorted position is g
+__device__ __forceinline__ unsigned long long free_word(const uint32_t *own, int g, int n, int w)
+{
+    const int rem = n - 64 * w;
+    const uint32_t b = (uint32_t)(g + (rem > 0 ? 64 * w : 0));
+    const uint32_t r0 = at(own, b >> 5), r1 = at(own, (b >> 5) + 1u), r2 = at(own, (b >> 5) + 2u);
+    const uint32_t lo = __builtin_amdgcn_alignbit(r1, r0, b & 31u), hi = __builtin_amdgcn_alignbit(r2, r1, b & 31u);
+    const unsigned long long m = ~(((unsigned long long)hi << 32) | lo);
+    return rem <= 0 ? 0ull : rem >= 64 ? m : m & ((1ull << rem) - 1ull);
+}
+
+__device__ __forceinline__ unsigned long long read_lane64(unsigned long long v, int l)
+{
+    const uint32_t a = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, l);
+    const uint32_t b = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), l);
+    return ((unsigned long long)b << 32) | a;
+}
+
+// minimum of (key, pos) over the lanes of a group: 4 << ls lanes for KQ = 4
+// (every lane gets it), else G lanes
+template <int KQ>
+__device__ __forceinline__ void group_min(unsigned long long &key, uint32_t &pos, int ls, int G)
+{
+    auto take = [&](uint32_t lo, uint32_t hi, uint32_t p) {
+        const unsigned long long o = ((unsigned long long)hi << 32) | lo;
+        const bool less = o < key;
+        key = less ? o : key;
+        pos = less ? p : pos;
+    };
+    if (KQ == 4) {
+        // quad_perm [1,0,3,2], [2,3,0,1], then the mirrors of 8 and of 16 lanes
+#define SBT_DPP3(CTRL)                                                                        \
+    take((uint32_t)quad_bcast<CTRL>((int)(uint32_t)key), (uint32_t)quad_bcast<CTRL>((int)(uint32_t)(key >> 32)), \
+         (uint32_t)quad_bcast<CTRL>((int)pos))
+        SBT_DPP3(0xB1);
+        SBT_DPP3(0x4E);
+        if (ls >= 1) SBT_DPP3(0x141);
+        if (ls >= 2) SBT_DPP3(0x140);
+#undef SBT_DPP3
+    } else {
+        for (int m = 1; m < G; m <<= 1)
+            take((uint32_t)lane_xor((int)(uint32_t)key, m), (uint32_t)lane_xor((int)(uint32_t)(key >> 32), m),
+                 (uint32_t)lane_xor((int)pos, m));
+    }
+}
+
+// The unflagged positions of a step's doublet and middle modules.  Lane w
+// holds word w of each; ex: unflagged positions before the word, A | Bm << 16.
+struct Free {
+    unsigned long long a, b;
+    int ex;
+    int na, nb;    // unflagged positions in all
+};
+
+// Seeding of step t (Section 3) on the waves from the last one down: modules
+// A = t-2, Bm = t-1, C = t; work items are (unflagged middle hit, partner
+// rank c).  With KQ = 4 a middle hit has 4 << ls lanes: the four partners, and
+// as many lanes per window walk as the workgroup has to spare (the walk, its
+// longest window among the wave's lanes, is what a step waits for).  Other K:
+// K adjacent lanes where K is a power of two up to 16, one lane otherwise.  A
+// new seed's search into t+1 runs on the lanes that made it; seed and result
+// go to the seeds table.  F: the unflagged positions of A, ascending.
+template <int B, int CAP, int KQ, bool kCand>
+__device__ __forceinline__ void seed_pass(uint32_t lo, const uint32_t *cand, const Step &st, Shared<B> &S,
+                                          const Free &fr, bool more, bool gc)
+{
+    const sbt_params &PP = kernel_params();
+    constexpr int NW = B / 64;
+    const int lane = (int)(tid<B>() & 63);
+    const int sw = NW - 1 - uni((int)(tid<B>() >> 6));
+    const int K = KQ ? KQ : PP.max_doublet_candidates;
+    const int ls = KQ == 4 ? (fr.nb * 16 <= B ? 2 : fr.nb * 8 <= B ? 1 : 0) : 0;
+    const int G = KQ == 4 ? 4 << ls : (K == 1 || K == 2 || K == 4 || K == 8 || K == 16) ? K : 1;
+    const int per_lane = KQ == 4 ? 1 : (G == 1 ? K : 1);
+    const int items = fr.nb * G;
+    if (sw * 64 >= items) return;
+
+    // the seeding waves carry the longest dependency chain of the step
+    __builtin_amdgcn_s_setprio(2);
+    const int na = st.n[2], nb = st.n[3], nf = fr.na;
+    const int Ws = opq(PP.phi_window_seeding), Wf = opq(PP.phi_window_forwarding);
+    const float Ss = opq(PP.max_scatter_seeding), Sf = opq(PP.max_scatter_forwarding);
+    const uint16_t *F = Lay<CAP>::freel(lo);
+    const LWin wa = lds_window<CAP>(lo, st.t - 2, na);
+    const LWin wc = lds_window<CAP>(lo, st.t, st.n[4]);
+    const Hit16 *hb = Lay<CAP>::ring(lo, (st.t - 1) & (kSlots - 1));
+    const int hd = na >> 1, hu = na - hd - 1;   // offsets visited: [-hd, hu]
+
+    for (int base = sw * 64; base < items; base += B) {
+        const int g = base + lane;
+        const bool on = g < items;
+        int i, c;
+        if (KQ == 4) {
+            i = g >> (2 + ls);
+            c = g & 3;
+        } else {
+            i = g / G;
+            c = g - i * G;
+        }
+        // the i-th unflagged position of Bm
+        int w = 0, r = i;
+        for (int x = 1; 64 * x < nb; ++x) {
+            const int f = __builtin_amdgcn_readlane(fr.ex, x) >> 16;
+            w = i >= f ? x : w;
+            r = i >= f ? i - f : r;
+        }
+        const uint32_t blo = (uint32_t)__shfl((int)(uint32_t)fr.b, w), bhi = (uint32_t)__shfl((int)(uint32_t)(fr.b >> 32), w);
+        const int p1 = on ? 64 * w + nth_set(((unsigned long long)bhi << 32) | blo, r) : 0;
+        const Hit16 h1 = at(hb, (uint32_t)p1);
+        // pendulum start: the first position of A whose phi16 is not below the middle hit's
+        int s0 = 0;
+        if (kCand) {
+            if (on) s0 = (int)at(cand, (uint32_t)(st.g[3] + p1));
+        } else if (KQ == 4) {
+            // the group's lanes test as many positions at a time
+            const uint32_t q1 = q_of(h1);
+            s0 = at(wa.tab, q1 >> wa.sh);
+            for (;;) {
+                const int x = s0 + (lane & (G - 1));
+                const bool less = x < na && q_of(at(wa.h, (uint32_t)(x < na ? x : 0))) < q1;
+                const uint32_t m = (uint32_t)(__ballot(less) >> (lane & (64 - G))) & ((1u << G) - 1u);
+                s0 += __popc(m);
+                if (__ballot(m == (1u << G) - 1u) == 0ull) break;
+            }
+            if (s0 == na) s0 = 0;
+        } else if (on) {
+            const uint32_t q1 = q_of(h1);
+            s0 = at(wa.tab, q1 >> wa.sh);
+            while (s0 < na && q_of(at(wa.h, (uint32_t)s0)) < q1) ++s0;
+            if (s0 == na) s0 = 0;
+        }
+        // unflagged positions below s0: the index in F of the first one at or
+        // above it (words from the lane that holds them, every lane active)
+        const int sl = s0 >> 6;
+        const uint32_t alo = (uint32_t)__shfl((int)(uint32_t)fr.a, sl), ahi = (uint32_t)__shfl((int)(uint32_t)(fr.a >> 32), sl);
+        const unsigned long long aw = ((unsigned long long)ahi << 32) | alo;
+        const int j = (__shfl(fr.ex, sl) & 0xFFFF) + __popcll(aw & ((1ull << (s0 & 63)) - 1ull));
+
+        unsigned long long bkey = ~0ull;
+        uint32_t bpos = 0;
+        for (int cc = 0; cc < per_lane; ++cc) {
+            const int pos0 = !on ? -1 : KQ == 4 ? pendulum_quad(F, nf, j, s0, na, hu, hd, c)
+                                                : pendulum_pick(F, nf, j, s0, na, hu, hd, c + cc);
+            if (pos0 < 0) break;
+            // best third hit of the doublet: the key orders like the comparison
+            // (found, scatter, id0, id2); positions pos0 | pos2 << 16.  Hits of
+            // C that are flagged hold no coordinate and fail the comparison.
+            const Hit16 h0 = at(wa.h, (uint32_t)pos0);
+            const uint32_t id0 = h0.qid >> 16;
+            const float d01 = h1.z - h0.z;
+            const float tx = (h1.x - h0.x) / d01;
+            const float ty = (h1.y - h0.y) / d01;
+            const float dzc = st.Zc - h1.z;
+            const uint32_t from = (uint32_t)(phi16(h1.x + tx * dzc, h1.y + ty * dzc) - Ws) & 0xFFFFu;
+            walk(wc, from, 2u * (uint32_t)Ws, KQ == 4 ? (lane >> 2) & ((1 << ls) - 1) : 0, 1 << ls,
+                 [&](const Hit16 &h2, int p, bool in) {
+                     const float dz = h2.z - h1.z;
+                     const float dx = (h1.x + tx * dz) - h2.x;
+                     const float dy = (h1.y + ty * dz) - h2.y;
+                     const float sc = (dx * dx) + (dy * dy);
+                     const unsigned long long key = ((unsigned long long)__float_as_uint(sc) << 32) |
+                                                    __builtin_amdgcn_alignbit(id0, h2.qid, 16);
+                     const bool better = in && sc < Ss && key < bkey;
+                     bkey = better ? key : bkey;
+                     bpos = better ? ((uint32_t)pos0 | ((uint32_t)p << 16)) : bpos;
+                 });
+        }
+        group_min<KQ>(bkey, bpos, ls, G);   // keys are unique or ~0
+        const bool found = bkey != ~0ull && on;
+        const int k = KQ == 4 ? lane & (G - 1) : c;   // lane of the group
+        const unsigned long long em = __ballot(found && k == 0);
+        if (em == 0ull) continue;
+        // the table's slots are taken before the search and needed after it
+        int slot = 0;
+        if (lane == 0) slot = atomicAdd(&S.ctl[st.t & 1], __popcll(em));
+        const uint32_t pos0 = bpos & 0xFFFFu, pos2 = bpos >> 16;
+        unsigned long long bk = ~0ull;
+        uint32_t pb = kNoPos;
+        const int u = st.t + 1;
+        if (more && st.n[5] > 0) {
+            if (found && (KQ == 4 || k == 0)) {
+                const Hit16 h2 = at(wc.h, pos2);
+                const float d12 = h2.z - h1.z;
+                const float tx = (h2.x - h1.x) / d12, ty = (h2.y - h1.y) / d12;
+                follow_walk(lds_window<CAP>(lo, u, st.n[5]), h2.x, h2.y, h2.z, tx, ty, st.Zn,
+                            Wf, Sf, KQ == 4 ? k : 0, KQ == 4 ? G : 1, bk, pb);
+            }
+            if (KQ == 4) group_min<KQ>(bk, pb, ls, G);
+        }
+        const float bsc = __uint_as_float((uint32_t)(bk >> 32));
+        slot = uni(slot);
+        if (found && k < 4 && (KQ == 4 || k == 0)) {
+            const int l = slot + lane_rank(em) - (k > 0 ? 1 : 0);
+            uint32_t *cl = Lay<CAP>::claim(lo);
+            uint32_t *sd = Lay<CAP>::seeds(lo, 0);
+            const uint32_t kap = claim32(bsc, u);
+            const uint32_t w0 = pos0 | ((uint32_t)p1 << 16), w1 = pos2 | (pb << 16), w2 = __float_as_uint(bsc);
+            const uint32_t a0 = (uint32_t)st.c[0] + pb, a1 = (uint32_t)st.c[2] + pos0, a2 = (uint32_t)(st.c[3] + p1),
+                           a3 = (uint32_t)st.c[4] + pos2;
+            const bool claims = pb != kNoPos && !gc;
+            bool tie = false;
+            if (KQ == 4) {
+                // a lane of the quad for each claim and each word
+                if (claims) tie = atomicMin(&cl[k == 0 ? a0 : k == 1 ? a1 : k == 2 ? a2 : a3], kap) == kap;
+                if (k < 3) sd[k * CAP + l] = k == 0 ? w0 : k == 1 ? w1 : w2;
+            } else {
+                if (claims) {
+                    const uint32_t o0 = atomicMin(&cl[a0], kap), o1 = atomicMin(&cl[a1], kap);
+                    const uint32_t o2 = atomicMin(&cl[a2], kap), o3 = atomicMin(&cl[a3], kap);
+                    tie = o0 == kap || o1 == kap || o2 == kap || o3 == kap;
+                }
+                sd[l] = w0;
+                sd[CAP + l] = w1;
+                sd[2 * CAP + l] = w2;
+            }
+            if (tie) S.ctl[2] = 1;
+        }
+    }
+    __builtin_amdgcn_s_setprio(0);
+}
+
+// hit i of a module, prefetched, and the word of the one before it
+struct Fetch {
+    Hit16 h;
+    uint32_t qp;
+};
+
+// Every lane loads (an idle one the module's first entry; the entry behind
+// the last module's is workspace memory too), so that nothing waits for the
+// load before the hit is put into the ring.
+__device__ __forceinline__ Fetch fetch_hit(const Hit16 *hs, int g, int n, int i)
+{
+    Fetch f;
+    const Hit16 *s = hs + g;
+    const uint32_t x = i < n ? (uint32_t)i : 0u;
+    f.h = at(s, x);
+    f.qp = at(s, x > 0u ? x - 1u : 0u).qid;
+    return f;
+}
+
+// The n sorted hits of traversal index u into its ring slot, their ids to
+// memory for the compaction, and the slot's coarse index: entry b is the
+// first position whose bin is b or above, so a position owns the bins above
+// its predecessor's up to its own, the last one also those above.
+template <int B, int CAP>
+__device__ __forceinline__ void ring_put(uint32_t lo, const Hit16 *hs, uint16_t *sid, int u, int g, int n, int i0,
+                                         const Fetch &f)
+{
+    Hit16 *ring = Lay<CAP>::ring(lo, u & (kSlots - 1));
+    uint16_t *tab = Lay<CAP>::tab(lo, u & (kSlots - 1));
+    sid += g;
+    const int sh = tab_shift(n);
+    if (i0 >= n) return;
+    Hit16 h = f.h;
+    uint32_t qp = f.qp;
+    asm volatile("" : "+v"(qp));   // keeps its use, and the wait for it, here
+    for (int i = i0; i < n; i += B) {
+        if (i != i0) {
+            h = at(hs + g, (uint32_t)i);
+            qp = at(hs + g, (uint32_t)(i - 1)).qid;
+        }
+        ring[i] = h;
+        at(sid, (uint32_t)i) = id_of(h);
+        const int own = (int)((h.qid & 0xFFFFu) >> sh);
+        for (int b = i > 0 ? (int)((qp & 0xFFFFu) >> sh) + 1 : 0; b <= own; ++b) tab[b] = (uint16_t)i;
+        if (i == n - 1)
+            for (int b = own + 1; b < (1 << (16 - sh)); ++b) tab[b] = (uint16_t)n;
+    }
+}
+
+// Takes the seeds of step t-1 into the free lanes.
+template <int B, int CAP, int SETS>
+__device__ __forceinline__ void take_seeds(uint32_t lo, const Step &st, Trk (&T)[SETS], const int (&base)[SETS], int nnew)
+{
+    const Hit16 *r1 = Lay<CAP>::ring(lo, (st.t - 2) & (kSlots - 1)), *r2 = Lay<CAP>::ring(lo, (st.t - 1) & (kSlots - 1));
+#pragma unroll
+    for (int s = 0; s < SETS; ++s) {
+        const unsigned long long fm = __ballot(T[s].lst == 0u);
+        const int l = base[s] + lane_rank(fm);
+        if (T[s].lst == 0u && l < nnew) {
+            const uint32_t a = Lay<CAP>::seeds(lo, 0)[l], b = Lay<CAP>::seeds(lo, 1)[l], c = Lay<CAP>::seeds(lo, 2)[l];
+            const Hit16 h1 = at(r1, a >> 16), h2 = at(r2, b & 0xFFFFu);
+            T[s].xa = h1.x; T[s].ya = h1.y; T[s].za = h1.z;
+            T[s].xb = h2.x; T[s].yb = h2.y; T[s].zb = h2.z;
+            const uint32_t p0 = (uint32_t)st.g[1] + (a & 0xFFFFu), p1 = (uint32_t)st.g[2] + (a >> 16),
+                           p2 = (uint32_t)st.g[3] + (b & 0xFFFFu);
+            T[s].k0 = (h1.qid >> 16) | (p0 << 16);
+            T[s].h12 = p1 | (p2 << 16);
+            T[s].lst = p2 | (3u << 16) | ((uint32_t)(st.t - 1) << 24);
+            T[s].pb = b >> 16;
+            T[s].bsc = __uint_as_float(c);
+        }
+    }
+}
+
+// Seeding and following over all modules with the windows in LDS.  Leaves
+// the final records (v.fin()) and their number in S.cnt[3], the flags by
+// sorted position in LDS (and in memory with writeback), the previous hit of
+// every appended hit in the links and the ids by sorted position in v.sid().
+// gc: every stage is settled over the words in memory (a bare seed may outlive
+// the claim slots).  Returns false when a step had more tracks than the lanes
+// hold; the event is then run again from memory.
+template <int B, int CAP, bool kCand>
+__device__ __forceinline__ bool track_lds(const Ev &v0, Shared<B> &S, bool writeback, bool gc)
+{
+    constexpr int NW = B / 64, SETS = track_sets<B, CAP>();
+    const int N = v0.N;
+    const int lane = (int)(tid<B>() & 63), wv = uni((int)(tid<B>() >> 6));
+    const int ri = (NW - 1 - wv) * 64 + lane;   // lanes counted from the last wave down
+    uint32_t *own = Lay<CAP>::own(v0.lo);
+    uint32_t *cl = Lay<CAP>::claim(v0.lo);
+    const int nw = (N + 31) >> 5;
+    const Hit16 *hs = v0.hs();
+    uint16_t *link = v0.link(), *sid = v0.sid();
+    Fin *fin = v0.fin();
+    unsigned long long *claim = v0.claim();
+    const uint32_t lo = v0.lo;
+    const uint32_t *cand = kCand ? v0.keys() : nullptr;   // pendulum starts of a candidate pass
+
+    Step st;
+    int last_seed = 2;
+    Trk T[SETS];
+    {
+    const sbt_params &PP = kernel_params();
+    const int M = PP.n_modules;
+    st.t = 2;
+    st.g[0] = st.g[1] = st.n[0] = st.n[1] = 0;
+#pragma unroll
+    for (int i = 2; i < 7; ++i) {
+        const int u = i - 2, k = u < M ? kmod(PP, u) : 0;
+        st.g[i] = uni(S.mo[k]);
+        st.n[i] = u < M ? uni(S.mo[k + 1] - S.mo[k]) : 0;
+    }
+    Fetch f0[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) f0[u] = fetch_hit(hs, st.g[u + 2], st.n[u + 2], ri);
+    for (int i = tid<B>(); i < nw + 2; i += B) at(own, i) = 0u;
+    for (int i = tid<B>(); i < kClaimSlots * CAP; i += B) cl[i] = 0xFFFFFFFFu;
+    for (int i = tid<B>(); i < N; i += B) at(reinterpret_cast<uint32_t *>(link), (uint32_t)i) = 0xFFFFFFFFu;
+    if (writeback)
+        for (int i = tid<B>(); i < N; i += B) at(claim, (uint32_t)i) = kNoClaim;
+    if (tid<B>() < NW) {
+        S.nfree[0][0][tid<B>()] = SETS >= 2 ? 64 | (64 << 16) : 64;
+        S.nfree[0][1][tid<B>()] = SETS >= 4 ? 64 | (64 << 16) : SETS == 3 ? 64 : 0;
+    }
+    if (tid<B>() < 4) S.ctl[tid<B>()] = 0;
+    if (tid<B>() < M) {
+        const int k = kmod(PP, (int)tid<B>());
+        S.mt[tid<B>()] = make_int4(S.mo[k], S.mo[k + 1] - S.mo[k], __float_as_int(PP.module_z[k]), 0);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+        if (u < M) ring_put<B, CAP>(lo, hs, sid, u, st.g[u + 2], st.n[u + 2], ri, f0[u]);
+    // the last traversal index whose seeding can make a seed: its modules
+    // t-2, t-1 and t all hold hits (2 when no index can)
+    {
+        const unsigned long long hold = __ballot(lane < M && S.mo[kmod(PP, lane < M ? lane : 0) + 1] > S.mo[kmod(PP, lane < M ? lane : 0)]);
+        const unsigned long long can = hold & (hold << 1) & (hold << 2);
+        if (can) last_seed = 63 - __builtin_clzll(can);
+    }
+#pragma unroll
+    for (int i = 0; i < 5; ++i) st.c[i] = ((st.t + 1 + i) % 5) * CAP;   // slot of t - 4 + i
+    st.Zc = PP.module_z[kmod(PP, 2)];
+    st.Zn = M > 3 ? PP.module_z[kmod(PP, 3)] : 0.0f;
+    st.Zx = M > 4 ? PP.module_z[kmod(PP, 4)] : 0.0f;
+#pragma unroll
+    for (int s = 0; s < SETS; ++s) T[s].lst = 0u;
+    }
+    ev_sync<B>();
+
+    // base[s]: free slots of set s before this wave's (sets in order, waves
+    // in order within a set); returns the number of free slots
+    auto free_slots = [&](const int (&fsl)[(SETS + 1) / 2], int (&base)[SETS]) -> int {
+        int total = 0;
+#pragma unroll
+        for (int h = 0; h < (SETS + 1) / 2; ++h) {
+            const int x = fsl[h];
+            const int inc = wave_incl_scan(x), ex = inc - x;
+            const int mine = __builtin_amdgcn_readlane(ex, wv), all = __builtin_amdgcn_readlane(inc, 63);
+            base[2 * h] = total + (mine & 0xFFFF);
+            total += all & 0xFFFF;
+            if (2 * h + 1 < SETS) {
+                base[2 * h + 1 < SETS ? 2 * h + 1 : 0] = total + (mine >> 16);
+                total += all >> 16;
+            }
+        }
+        return total;
+    };
+    auto finish = [&](Trk &t, bool done) {
+        const int r = wave_append(done, &S.ctl[3]);
+        if (done) {
+            Fin w;
+            w.x = t.k0;
+            w.y = t.h12;
+            w.z = t.lst & 0xFFFFFFu;
+            w.w = 0;
+            at(fin, (uint32_t)r) = w;
+            t.lst = 0u;
+        }
+    };
+    Fetch f;
+    bool ended = false, cleared = writeback;   // claims in memory: whether they have been cleared
+    for (;;) {
+        // ---- S(t)
+        const sbt_params &PP = kernel_params();
+        const int misses = PP.max_consecutive_misses;
+        const bool more = st.t + 1 < PP.n_modules;
+        f = fetch_hit(hs, st.g[6], st.n[6], ri);   // module t+2, put into the ring in R(t+1)
+        if (st.n[2] > 0 && st.n[3] > 0 && st.n[4] > 0) {
+            Free fr;
+            fr.a = free_word(own, st.g[2], st.n[2], lane);
+            fr.b = free_word(own, st.g[3], st.n[3], lane);
+            const int pc = __popcll(fr.a) | (__popcll(fr.b) << 16);
+            const int inc = wave_incl_scan(pc);
+            const int tot = __builtin_amdgcn_readlane(inc, 63);
+            fr.ex = inc - pc;
+            fr.na = tot & 0xFFFF;
+            fr.nb = tot >> 16;
+            if (fr.na > 0 && fr.nb > 0) {
+                // the list of A's unflagged positions, a word per wave and round
+                uint16_t *F = Lay<CAP>::freel(lo);
+                for (int w = wv; 64 * w < st.n[2]; w += NW) {
+                    const unsigned long long m = read_lane64(fr.a, w);
+                    const int at0 = __builtin_amdgcn_readlane(fr.ex, w) & 0xFFFF;
+                    if ((m >> lane) & 1ull) at(F, (uint32_t)(at0 + lane_rank(m))) = (uint16_t)(64 * w + lane);
+                }
+                ev_lds_sync<B>();
+                if (PP.max_doublet_candidates == 4) seed_pass<B, CAP, 4, kCand>(lo, cand, st, S, fr, more, gc);
+                else seed_pass<B, CAP, 0, kCand>(lo, cand, st, S, fr, more, gc);
+            }
+        }
+        if (more) {
+            const int u = st.t + 1, Wf = opq(PP.phi_window_forwarding);
+            const float Sf = opq(PP.max_scatter_forwarding);
+            const LWin wn = lds_window<CAP>(lo, u, st.n[5]);
+#pragma unroll
+            for (int s = 0; s < SETS; ++s) {
+                Trk &t = T[s];
+                if (__ballot(t.lst != 0u) == 0ull) continue;
+                t.pb = kNoPos;
+                const int last_t = (int)(t.lst >> 24);
+                const bool bare = ((t.lst >> 16) & 0xFFu) == 3u;
+                const uint32_t p0 = t.k0 >> 16, p1 = t.h12 & 0xFFFFu, p2 = t.h12 >> 16;
+                bool elig = t.lst != 0u && u - last_t <= misses + 1 && wn.n > 0;
+                if (elig && bare) elig = is_free(own, p0) && is_free(own, p1) && is_free(own, p2);
+                if (elig) {
+                    const float dab = t.zb - t.za;
+                    const float tx = (t.xb - t.xa) / dab, ty = (t.yb - t.ya) / dab;
+                    unsigned long long bk = ~0ull;
+                    follow_walk(wn, t.xb, t.yb, t.zb, tx, ty, st.Zn, Wf, Sf, 0, 1, bk, t.pb);
+                    t.bsc = __uint_as_float((uint32_t)(bk >> 32));
+                    if (t.pb != kNoPos && !gc) {
+                        // a kept bare seed was made at t-1: its hits are in t-3, t-2 and t-1
+                        const uint32_t kap = claim32(t.bsc, u);
+                        bool tie = atomicMin(&cl[(uint32_t)st.c[0] + t.pb], kap) == kap;
+                        if (bare) {
+                            const uint32_t o0 = atomicMin(&cl[st.c[1] + ((int)p0 - st.g[1])], kap);
+                            const uint32_t o1 = atomicMin(&cl[st.c[2] + ((int)p1 - st.g[2])], kap);
+                            const uint32_t o2 = atomicMin(&cl[st.c[3] + ((int)p2 - st.g[3])], kap);
+                            tie = tie || o0 == kap || o1 == kap || o2 == kap;
+                        }
+                        if (tie) S.ctl[2] = 1;
+                    }
+                }
+            }
+        }
+        ev_lds_sync<B>();
+        // ---- on to t+1
+        {
+        const sbt_params &PP = kernel_params();
+        const int M = PP.n_modules, misses = PP.max_consecutive_misses;
+        st.t += 1;
+        // everything the step's scalars come from, in one round of loads
+        const int4 ctl = *reinterpret_cast<const int4 *>(S.ctl);
+        const int4 nxt = S.mt[st.t + 2 < M ? st.t + 2 : 0];
+        int fsl[(SETS + 1) / 2];
+#pragma unroll
+        for (int h = 0; h < (SETS + 1) / 2; ++h) fsl[h] = lane < NW ? S.nfree[(st.t + 1) & 1][h][lane] : 0;
+#pragma unroll
+        for (int i = 0; i < 6; ++i) {
+            st.g[i] = st.g[i + 1];
+            st.n[i] = st.n[i + 1];
+        }
+        {
+            const int c0 = st.c[0];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) st.c[i] = st.c[i + 1];
+            st.c[4] = c0;
+        }
+        st.Zc = st.Zn;
+        st.Zn = st.Zx;
+        st.g[6] = uni(nxt.x);
+        st.n[6] = st.t + 2 < M ? uni(nxt.y) : 0;
+        st.Zx = __int_as_float(uni(nxt.z));
+        const int t = st.t;
+        int base[SETS];
+        const int nnew = uni((t - 1) & 1 ? ctl.y : ctl.x);
+        const int nfree = free_slots(fsl, base);
+        const bool exact = gc || uni(ctl.z) != 0;
+        if (nnew > nfree) return false;
+        const bool end = t >= M;
+        // with no forming track and no seed possible from here on, the
+        // remaining steps change nothing
+        ended = end || (nnew == 0 && nfree == SETS * B && t > last_seed);
+        if (nnew > 0) take_seeds<B, CAP, SETS>(lo, st, T, base, nnew);
+        if (ended) break;
+        // ---- R(t)
+        if (t + 1 < M) ring_put<B, CAP>(lo, hs, sid, t + 1, st.g[5], st.n[5], ri, f);
+        if (exact) {
+            // the claims of this stage over again as 64-bit words in memory
+            if (!cleared)
+                for (int i = tid<B>(); i < N; i += B) at(claim, (uint32_t)i) = kNoClaim;
+            cleared = true;
+            ev_sync<B>();
+            if (tid<B>() == 0) S.ctl[2] = 0;
+#pragma unroll
+            for (int s = 0; s < SETS; ++s) {
+                const Trk &k = T[s];
+                if (k.lst == 0u || k.pb == kNoPos) continue;
+                const unsigned long long kap = claim_key(k.bsc, (uint16_t)(k.k0 & 0xFFFFu), t);
+                atomicMin(&at(claim, (uint32_t)st.g[4] + k.pb), kap);
+                if (((k.lst >> 16) & 0xFFu) == 3u) {
+                    atomicMin(&at(claim, k.k0 >> 16), kap);
+                    atomicMin(&at(claim, k.h12 & 0xFFFFu), kap);
+                    atomicMin(&at(claim, k.h12 >> 16), kap);
+                }
+            }
+            ev_sync<B>();
+        }
+        Hit16 *rt = Lay<CAP>::ring(lo, t & (kSlots - 1));
+        int nf[(SETS + 1) / 2 * 2] = {};
+#pragma unroll
+        for (int s = 0; s < SETS; ++s) {
+            Trk &k = T[s];
+            const bool act = k.lst != 0u;
+            if (__ballot(act) == 0ull) {
+                nf[s] = 64;
+                continue;
+            }
+            const int last_t0 = (int)(k.lst >> 24);
+            const bool bare = ((k.lst >> 16) & 0xFFu) == 3u;
+            const uint32_t p0 = k.k0 >> 16, p1 = k.h12 & 0xFFFFu, p2 = k.h12 >> 16;
+            bool win = false;
+            if (act && k.pb != kNoPos) {
+                if (exact) {
+                    const unsigned long long kap = claim_key(k.bsc, (uint16_t)(k.k0 & 0xFFFFu), t);
+                    win = at(claim, (uint32_t)st.g[4] + k.pb) == kap;
+                    if (bare) win = win && at(claim, p0) == kap && at(claim, p1) == kap && at(claim, p2) == kap;
+                } else {
+                    const uint32_t kap = claim32(k.bsc, t);
+                    win = cl[(uint32_t)st.c[4] + k.pb] == kap;
+                    if (bare) {
+                        // made at t-1 (hits in t-3 .. t-1) or at t-2 (t-4 .. t-2)
+                        const bool s1 = last_t0 == t - 1;
+                        const int b0 = s1 ? st.c[1] - st.g[1] : st.c[0] - st.g[0];
+                        const int b1 = s1 ? st.c[2] - st.g[2] : st.c[1] - st.g[1];
+                        const int b2 = s1 ? st.c[3] - st.g[3] : st.c[2] - st.g[2];
+                        const uint32_t o0 = cl[b0 + (int)p0], o1 = cl[b1 + (int)p1], o2 = cl[b2 + (int)p2];
+                        win = win && o0 == kap && o1 == kap && o2 == kap;
+                    }
+                }
+            }
+            if (win) {
+                const uint32_t p = (uint32_t)st.g[4] + k.pb;
+                set_flag(own, p);
+                if (bare) {
+                    set_flag(own, p0);
+                    set_flag(own, p1);
+                    set_flag(own, p2);
+                }
+                at(link, 2u * p) = (uint16_t)(k.lst & 0xFFFFu);
+                const Hit16 h = at(rt, k.pb);
+                // a flagged hit loses its coordinate here, so that the seeding
+                // walk over this module passes it by (nothing else reads it)
+                at(rt, k.pb).x = __builtin_nanf("");
+                k.xa = k.xb; k.ya = k.yb; k.za = k.zb;
+                k.xb = h.x; k.yb = h.y; k.zb = h.z;
+                k.lst = p | ((((k.lst >> 16) & 0xFFu) + 1u) << 16) | ((uint32_t)t << 24);
+            }
+            const bool done = k.lst != 0u && t - (int)(k.lst >> 24) >= misses + 1;
+            if (__ballot(done) != 0ull) finish(k, done);
+            nf[s] = __popcll(__ballot(k.lst == 0u));
+        }
+        if (lane == 0) {
+#pragma unroll
+            for (int h = 0; h < (SETS + 1) / 2; ++h) S.nfree[t & 1][h][wv] = nf[2 * h] | (nf[2 * h + 1] << 16);
+            if (wv == 0) S.ctl[t & 1] = 0;
+        }
+        ev_lds_sync<B>();
+        }
+    }
+#pragma unroll
+    for (int s = 0; s < SETS; ++s)
+        if (__ballot(T[s].lst != 0u) != 0ull) finish(T[s], T[s].lst != 0u);
+    if (writeback)
+        for (int i = tid<B>(); i < nw; i += B) at(v0.own(), i) = at(own, i);
+    ev_sync<B>();
+    if (tid<B>() == 0) S.cnt[3] = S.ctl[3];
+    ev_sync<B>();
+    return true;
+}
+
+// ================================================================ memory form
 // Best third hit for one doublet: the key orders like the comparison
 // (found, scatter, id0, id2) -- scatter bits << 32 | id0 << 16 | id2, ~0 when
 // nothing was found (scatters are >= +0, so their bits order like the
 // values); pos holds the window positions pos0 | pos2 << 16.
-template <bool kLds>
-__device__ __forceinline__ void seed_doublet(const Win &wa, const Win &wc, const uint32_t *own,
-                                             const unsigned long long *cfree, int pos0, float x1, float y1, float z1,
-                                             float Zc, float Ss, uint16_t Ws, uint16_t span, unsigned long long &bkey,
-                                             uint32_t &bpos)
+__device__ __forceinline__ void seed_doublet(const Win &wa, const Win &wc, const uint32_t *own, int pos0, float x1,
+                                             float y1, float z1, float Zc, float Ss, uint16_t Ws, uint16_t span,
+                                             unsigned long long &bkey, uint32_t &bpos)
 {
     const Hit16 h0 = at(wa.h, pos0);
     const uint32_t id0 = id_of(h0);
@@ -1006,43 +1715,35 @@ __device__ __forceinline__ void seed_doublet(const Win &wa, const Win &wc, const
     const int nc = wc.n;
     if (nc == 0) return;
     const uint16_t lo = (uint16_t)(qe - Ws);
-    int pc = win_lower_bound<kLds>(wc, lo);
+    int pc = win_lower_bound(wc, lo);
     if (pc == nc) pc = 0;
     Hit16 h2n = at(wc.h, pc);
     for (int jj = 0; jj < nc; ++jj) {
-        // LDS: the flag bit is addressed by position, so it loads alongside the hit
-        const bool fpos = kLds ? ((at(cfree, (uint32_t)pc >> 6) >> (pc & 63)) & 1ull) != 0ull : true;
         const Hit16 h2 = h2n;
         const int pn = pc + 1 == nc ? 0 : pc + 1;
         h2n = at(wc.h, pn);   // the next position, loaded while this one is scored
         if ((uint16_t)(q_of(h2) - lo) > span) break;
         const uint32_t id2 = id_of(h2);
-        const bool fr = kLds ? fpos : is_free(own, id2);
         const float dz = h2.z - z1;
         const float dx = (x1 + tx * dz) - h2.x;
         const float dy = (y1 + ty * dz) - h2.y;
         const float sc = (dx * dx) + (dy * dy);
         const unsigned long long k = ((unsigned long long)__float_as_uint(sc) << 32) | (id0 << 16) | id2;
-        const bool better = fr && (sc < Ss) && (k < bkey);
+        const bool better = is_free(own, id2) && (sc < Ss) && (k < bkey);
         bkey = better ? k : bkey;
         bpos = better ? ((uint32_t)pos0 | ((uint32_t)pc << 16)) : bpos;
         pc = pn;
     }
 }
 
-// ---------------------------------------------------------------- following search
 // Following search of one forming track into traversal index u (Section 3,
 // "track following"): the last two hits extrapolated to the module's
 // nominal z, the best unflagged hit of the inclusive phi window by
 // (scatter, id) under the threshold, and claims on that hit (and on the
-// three seed hits of a bare seed) keyed (scatter, key) for stage u.  The LDS
-// instantiation claims the best hit in lclaim, by window position; seed
-// hits are always claimed in memory.  Returns the best hit's id | window
-// position << 16, or ~0.
-template <bool kLds>
+// three seed hits of a bare seed) keyed (scatter, key) for stage u.  Returns
+// the best hit's id | window position << 16, or ~0.
 __device__ __forceinline__ uint32_t follow_item(const Prm &P, const Win &wc, float Zc, const uint32_t *own,
-                                                unsigned long long *claim, unsigned long long *lclaim, const Rec &R,
-                                                int u, float &bsc_out)
+                                                unsigned long long *claim, const Rec &R, int u, float &bsc_out)
 {
     const float Sf = P.Sf;
     const uint16_t Wf = (uint16_t)P.Wf;
@@ -1057,7 +1758,7 @@ __device__ __forceinline__ uint32_t follow_item(const Prm &P, const Win &wc, flo
         const float dzc = Zc - R.zb;
         const uint16_t qe = phi16(R.xb + R.tx * dzc, R.yb + R.ty * dzc);
         const uint16_t lo = (uint16_t)(qe - Wf);
-        int pc = win_lower_bound<kLds>(wc, lo);
+        int pc = win_lower_bound(wc, lo);
         if (pc == nc) pc = 0;
         // No hit of module u is flagged yet: flags are set only when a
         // module is resolved, and u is resolved after this search.  The
@@ -1086,8 +1787,7 @@ __device__ __forceinline__ uint32_t follow_item(const Prm &P, const Win &wc, flo
         }
         if (best != kNone) {
             const unsigned long long kap = claim_key(bsc, R.key, u);
-            if (kLds) atomicMin(&lclaim[bpos], kap);
-            else atomicMin(&at(claim, best), kap);
+            atomicMin(&at(claim, best), kap);
             if (R.len == 3) {
                 atomicMin(&at(claim, R.h0), kap);
                 atomicMin(&at(claim, R.h1), kap);
@@ -1099,52 +1799,31 @@ __device__ __forceinline__ uint32_t follow_item(const Prm &P, const Win &wc, flo
     return best == kNone ? 0xFFFFFFFFu : ((uint32_t)bpos << 16) | best;
 }
 
-// Search result of active slot a (record r).  LDS instantiation: the slot's
-// 16 bytes hold the result and what the resolution needs to test the claims
-// without the record: {best | position << 16, scatter, key | h0 << 16,
-// h1 | h2 << 16}, seed hits only for a bare seed (h0 = none otherwise).
-// Memory instantiation: the record's auxiliary data.
-template <bool kLds, int CAP>
-__device__ __forceinline__ void put_result(const Ev &v, int a, int r, uint32_t pb, float bsc, const Rec &R)
-{
-    if (kLds) {
-        uint4 w;
-        w.x = pb;
-        w.y = __float_as_uint(bsc);
-        w.z = (uint32_t)R.key | ((uint32_t)(R.len == 3 ? R.h0 : kNone) << 16);
-        w.w = (uint32_t)R.h1 | ((uint32_t)R.h2 << 16);
-        Lay<CAP>::res(v.lo)[a] = w;
-    } else {
-        RecAux &x = at(v.aux(), r);
-        x.best = pb;
-        x.bsc = bsc;
-    }
-}
-
 // Seeding(t), t >= 2 (Section 3), fused with the following search into
 // t+1.  With kCand the pendulum start of every middle hit is read from the
 // table a separate candidate pass wrote into the workspace (the paper's
-// "Fill candidates" kernel) instead of being searched here.  Seeding: modules A = kmod(t-2), Bm = kmod(t-1), C = kmod(t); work
-// items are (unflagged middle hit, partner rank c) -- with K a power of two
-// up to 16, the K doublets of a middle hit run on K adjacent lanes and their
-// best triplets are reduced across the lanes, otherwise one lane handles all
-// K.  A new seed's following search into t+1 runs on the lane that made it.
-// The tracks kept by the last resolution (active slots [0, n_keep)) search
-// t+1 on waves of their own.  Both read the flags as the resolution of t
-// left them, which is the state the following of t+1 starts from.
-template <int B, bool kLds, int CAP, bool kCand = false>
-__device__ void stage_seed_follow(const sbt_params &PP, const Ev &v0, int t, Shared<B> &S, const uint32_t *own,
+// "Fill candidates" kernel) instead of being searched here.  Seeding: modules
+// A = kmod(t-2), Bm = kmod(t-1), C = kmod(t); work items are (unflagged middle
+// hit, partner rank c) -- with K a power of two up to 16, the K doublets of a
+// middle hit run on K adjacent lanes and their best triplets are reduced
+// across the lanes, otherwise one lane handles all K.  A new seed's following
+// search into t+1 runs on the lane that made it.  The tracks kept by the last
+// resolution (active slots [0, n_keep)) search t+1 on waves of their own.
+// Both read the flags as the resolution of t left them, which is the state
+// the following of t+1 starts from.
+template <int B, bool kCand>
+__device__ __forceinline__ void stage_seed_follow(const sbt_params &PP, const Ev &v0, int t, Shared<B> &S, const uint32_t *own,
                                   uint16_t *nxt, int *n_nxt, int n_keep, bool follow_next)
 {
     const Prm P = fresh(PP);
     const Ev v = fresh(v0);
-    const Win wa = window<B, kLds, CAP>(P, S, v, t - 2);
-    const Win wb = window<B, kLds, CAP>(P, S, v, t - 1);
-    const Win wc = window<B, kLds, CAP>(P, S, v, t);
+    const Win wa = window<B>(P, S, v, t - 2);
+    const Win wb = window<B>(P, S, v, t - 1);
+    const Win wc = window<B>(P, S, v, t);
     Win wn = wc;
     float Zn = 0.0f;
     if (follow_next) {
-        wn = window<B, kLds, CAP>(P, S, v, t + 1);
+        wn = window<B>(P, S, v, t + 1);
         Zn = PP.module_z[kmod(P, t + 1)];
     }
     const int na = wa.n, nbm = wb.n;
@@ -1155,33 +1834,17 @@ __device__ void stage_seed_follow(const sbt_params &PP, const Ev &v0, int t, Sha
     const uint16_t span = (uint16_t)(2 * P.Ws);
 
     // unflagged positions of the doublet module and of the middle module, ascending
-    uint16_t *F, *FR, *FM;
-    if (kLds) {
-        F = Lay<CAP>::freel(v.lo);
-        FR = Lay<CAP>::frank(v.lo);
-        FM = Lay<CAP>::freem(v.lo);
-    } else {
-        const int ga = uni(S.mo[kmod(P, t - 2)]), gb = uni(S.mo[kmod(P, t - 1)]);
-        F = v.list(kListFreeL) + ga;
-        FR = v.list(kListFRank) + ga;
-        FM = v.list(kListFreeM) + gb;
-    }
+    const int ga = uni(S.mo[kmod(P, t - 2)]), gb = uni(S.mo[kmod(P, t - 1)]);
+    uint16_t *F = v.list(kListFreeL) + ga;
+    uint16_t *FR = v.list(kListFRank) + ga;
+    uint16_t *FM = v.list(kListFreeM) + gb;
     int nf = 0, nfm = 0;
-    int nmax = na > nbm ? na : nbm;
-    if (kLds && wc.n > nmax) nmax = wc.n;
-    unsigned long long *cfree = kLds ? Lay<CAP>::cfree(v.lo) : nullptr;
-    unsigned long long *lclaim = kLds ? Lay<CAP>::lclaim(v.lo) : nullptr;
-    if (kLds && follow_next)
-        for (int p = tid<B>(); p < wn.n; p += B) lclaim[p] = kNoClaim;
+    const int nmax = na > nbm ? na : nbm;
     int phase = 0;
     for (int base = 0; base < nmax; base += B, ++phase) {
         const int p = base + (int)tid<B>();
         const bool fa = p < na && is_free(own, win_id(wa, p));
         const bool fb = p < nbm && is_free(own, win_id(wb, p));
-        if (kLds) {
-            const unsigned long long m = __ballot(p < wc.n && is_free(own, win_id(wc, p)));
-            if ((tid<B>() & 63) == 0 && p < wc.n) at(cfree, (uint32_t)p >> 6) = m;
-        }
         int total;
         const int idx = block_count2<B>(fa, fb, S.scan, phase, &total);
         if (p < na) at(FR, p) = (uint16_t)(nf + (idx & 0xFFFF));
@@ -1190,9 +1853,7 @@ __device__ void stage_seed_follow(const sbt_params &PP, const Ev &v0, int t, Sha
         nf += total & 0xFFFF;
         nfm += total >> 16;
     }
-    // the lists are in LDS in the LDS instantiation, in memory otherwise
-    if (kLds) ev_lds_sync<B>();
-    else ev_sync<B>();
+    ev_sync<B>();
     const int hd = na >> 1, hu = na - hd - 1;   // offsets visited: [-hd, hu]
     const int G = (K == 1 || K == 2 || K == 4 || K == 8 || K == 16) ? K : 1;
     const int per_lane = G == 1 ? K : 1;
@@ -1210,8 +1871,10 @@ __device__ void stage_seed_follow(const sbt_params &PP, const Ev &v0, int t, Sha
                 const int r = at(nxt, a);
                 const Rec R = at(v.rec(), r);
                 float bsc;
-                const uint32_t pb = follow_item<kLds>(P, wn, Zn, own, v.claim(), lclaim, R, t + 1, bsc);
-                put_result<kLds, CAP>(v, a, r, pb, bsc, R);
+                const uint32_t pb = follow_item(P, wn, Zn, own, v.claim(), R, t + 1, bsc);
+                RecAux &x = at(v.aux(), r);
+                x.best = pb;
+                x.bsc = bsc;
             }
             continue;
         }
@@ -1228,21 +1891,20 @@ __device__ void stage_seed_follow(const sbt_params &PP, const Ev &v0, int t, Sha
             h1 = at(wb.h, p1);
             int s0;
             if (kCand) {
-                s0 = (int)at(v.keys(), (uint32_t)(uni(S.mo[kmod(P, t - 1)]) + p1));
+                s0 = (int)at(v.keys(), (uint32_t)(gb + p1));
             } else {
-                s0 = win_lower_bound<kLds>(wa, q_of(h1));
+                s0 = win_lower_bound(wa, q_of(h1));
                 if (s0 == na) s0 = 0;
             }
             const int j = at(FR, s0);   // first unflagged position >= s0, as an index into F
             if (G == 4) {
                 const int pos0 = pendulum_quad(F, nf, j, s0, na, hu, hd, c);
-                if (pos0 >= 0)
-                    seed_doublet<kLds>(wa, wc, own, cfree, pos0, h1.x, h1.y, h1.z, Zc, Ss, Ws, span, bkey, bpos);
+                if (pos0 >= 0) seed_doublet(wa, wc, own, pos0, h1.x, h1.y, h1.z, Zc, Ss, Ws, span, bkey, bpos);
             } else {
                 for (int cc = 0; cc < per_lane; ++cc) {
                     const int pos0 = pendulum_pick(F, nf, j, s0, na, hu, hd, c + cc);
                     if (pos0 < 0) break;
-                    seed_doublet<kLds>(wa, wc, own, cfree, pos0, h1.x, h1.y, h1.z, Zc, Ss, Ws, span, bkey, bpos);
+                    seed_doublet(wa, wc, own, pos0, h1.x, h1.y, h1.z, Zc, Ss, Ws, span, bkey, bpos);
                 }
             }
         }
@@ -1261,35 +1923,26 @@ __device__ void stage_seed_follow(const sbt_params &PP, const Ev &v0, int t, Sha
         int r, l;
         wave_append2(emit, &S.cnt[0], emit, n_nxt, r, l);
         if (emit) {
-            if (kLds && l >= CAP) {
-                S.ovf = 1;
-            } else {
-                const int pos0 = (int)(bpos & 0xFFFFu), pos2 = (int)(bpos >> 16);
-                const Hit16 h0 = at(wa.h, pos0);
-                const Hit16 h2 = at(wc.h, pos2);
-                const float x1 = h1.x, y1 = h1.y, z1 = h1.z;
-                Rec R;
-                const float d12 = h2.z - z1;
-                R.xb = h2.x; R.yb = h2.y; R.zb = h2.z;
-                R.tx = (h2.x - x1) / d12;
-                R.ty = (h2.y - y1) / d12;
-                R.key = id_of(h1); R.h0 = id_of(h0); R.h1 = id_of(h1); R.h2 = id_of(h2); R.last = id_of(h2);
-                R.len = 3; R.last_t = (uint8_t)t;
-                at(v.rec(), r) = R;
-                // tracklet fit of the seed, hits in traversal order (Section 3,
-                // "Tracklet filter"): chi2 = ((v.x)^2 + (v.y)^2) / (v.v) with
-                // v = (z2-z1, z0-z2, z1-z0) orthogonal to (1,1,1) and to z
-                const float v0 = h2.z - z1, v1 = h0.z - h2.z, v2 = z1 - h0.z;
-                const float ssx = ((v0 * h0.x) + (v1 * x1)) + (v2 * h2.x);
-                const float ssy = ((v0 * h0.y) + (v1 * y1)) + (v2 * h2.y);
-                const float n2 = ((v0 * v0) + (v1 * v1)) + (v2 * v2);
-                at(v.aux(), r).chi2 = ((ssx * ssx) + (ssy * ssy)) / n2;
-                at(nxt, l) = (uint16_t)r;
-                if (follow_next) {
-                    float bsc;
-                    const uint32_t pb = follow_item<kLds>(P, wn, Zn, own, v.claim(), lclaim, R, t + 1, bsc);
-                    put_result<kLds, CAP>(v, l, r, pb, bsc, R);
-                }
+            const int pos0 = (int)(bpos & 0xFFFFu), pos2 = (int)(bpos >> 16);
+            const Hit16 h0 = at(wa.h, pos0);
+            const Hit16 h2 = at(wc.h, pos2);
+            const float x1 = h1.x, y1 = h1.y, z1 = h1.z;
+            Rec R;
+            const float d12 = h2.z - z1;
+            R.xb = h2.x; R.yb = h2.y; R.zb = h2.z;
+            R.tx = (h2.x - x1) / d12;
+            R.ty = (h2.y - y1) / d12;
+            R.key = id_of(h1); R.h0 = id_of(h0); R.h1 = id_of(h1); R.h2 = id_of(h2); R.last = id_of(h2);
+            R.len = 3; R.last_t = (uint8_t)t;
+            at(v.rec(), r) = R;
+            at(v.aux(), r).chi2 = seed_chi2(h0, h1, h2);
+            at(nxt, l) = (uint16_t)r;
+            if (follow_next) {
+                float bsc;
+                const uint32_t pb = follow_item(P, wn, Zn, own, v.claim(), R, t + 1, bsc);
+                RecAux &x = at(v.aux(), r);
+                x.best = pb;
+                x.bsc = bsc;
             }
         }
         __builtin_amdgcn_s_setprio(0);
@@ -1300,13 +1953,13 @@ __device__ void stage_seed_follow(const sbt_params &PP, const Ev &v0, int t, Sha
 // append their best hit and flag their claim set.  Tracks that have now missed
 // more than max_consecutive_misses modules in a row become final; the others
 // stay active for the next module.
-template <int B, bool kLds, int CAP>
-__device__ void stage_follow_resolve(const sbt_params &PP, const Ev &v0, int t, Shared<B> &S, uint32_t *own,
+template <int B>
+__device__ __forceinline__ void stage_follow_resolve(const sbt_params &PP, const Ev &v0, int t, Shared<B> &S, uint32_t *own,
                                      const uint16_t *act, int n_act, uint16_t *nxt, int *n_nxt)
 {
     const Prm P = fresh(PP);
     const Ev v = fresh(v0);
-    const Win wc = window<B, kLds, CAP>(P, S, v, t);
+    const Win wc = window<B>(P, S, v, t);
     const unsigned long long *__restrict__ claim = v.claim();
     uint16_t *fin = v.list(kListFin);
     for (int base = 0; base < n_act; base += B) {
@@ -1315,37 +1968,20 @@ __device__ void stage_follow_resolve(const sbt_params &PP, const Ev &v0, int t, 
         int r = 0;
         if (a < n_act) {
             r = at(act, a);
-            uint32_t pb, k0 = 0, k12 = 0;
-            float bsc;
-            if (kLds) {
-                const uint4 w = Lay<CAP>::res(v.lo)[a];
-                pb = w.x;
-                bsc = __uint_as_float(w.y);
-                k0 = w.z;
-                k12 = w.w;
-            } else {
-                const RecAux &x = at(v.aux(), r);
-                pb = x.best;
-                bsc = x.bsc;
-            }
+            const RecAux &x = at(v.aux(), r);
+            const uint32_t pb = x.best;
+            const float bsc = x.bsc;
             Rec R = at(v.rec(), r);
-            if (!kLds) {
-                k0 = (uint32_t)R.key | ((uint32_t)(R.len == 3 ? R.h0 : kNone) << 16);
-                k12 = (uint32_t)R.h1 | ((uint32_t)R.h2 << 16);
-            }
+            const uint16_t best = (uint16_t)(pb & 0xFFFF);
             bool win = false;
             if (pb != 0xFFFFFFFFu) {
-                const uint16_t best = (uint16_t)(pb & 0xFFFF);
-                const unsigned long long kap = claim_key(bsc, (uint16_t)(k0 & 0xFFFFu), t);
-                const uint16_t h0 = (uint16_t)(k0 >> 16);
-                win = kLds ? Lay<CAP>::lclaim(v.lo)[pb >> 16] == kap : at(claim, best) == kap;
-                if (h0 != kNone)
-                    win = win && at(claim, h0) == kap && at(claim, (uint16_t)(k12 & 0xFFFFu)) == kap &&
-                          at(claim, (uint16_t)(k12 >> 16)) == kap;
+                const unsigned long long kap = claim_key(bsc, R.key, t);
+                win = at(claim, best) == kap;
+                if (R.len == 3)
+                    win = win && at(claim, R.h0) == kap && at(claim, R.h1) == kap && at(claim, R.h2) == kap;
             }
             int last_t = R.last_t;
             if (win) {
-                const uint16_t best = (uint16_t)(pb & 0xFFFF);
                 const int bpos = (int)(pb >> 16);
                 set_flag(own, best);
                 if (R.len == 3) {
@@ -1371,30 +2007,18 @@ __device__ void stage_follow_resolve(const sbt_params &PP, const Ev &v0, int t, 
         int f, l;
         wave_append2(done, &S.cnt[3], keep, n_nxt, f, l);
         if (done) at(fin, f) = (uint16_t)r;
-        if (keep) {
-            if (kLds && l >= CAP) S.ovf = 1;
-            else at(nxt, l) = (uint16_t)r;
-        }
+        if (keep) at(nxt, l) = (uint16_t)r;
     }
 }
 
-// whether an event fits the LDS instantiation of the tracking stages
-template <int B, int CAP>
-__device__ __forceinline__ bool event_fits_lds(const Shared<B> &S, int N, int own_cap)
-{
-    return CAP > 0 && uni(S.maxmod) <= CAP && N <= own_cap;
-}
-
-// Seeding and following over all modules.  Leaves the final record list in
-// the final list and its length in S.cnt[3]; with writeback the LDS flags are
-// copied to memory.  The LDS instantiation returns false when an active list
-// outgrew its LDS capacity (the event is then run again from memory).
-template <int B, bool kLds, int CAP, bool kCand = false>
-__device__ bool stage_track_impl(const sbt_params &PP, const Ev &v, Shared<B> &S, bool writeback)
+// Seeding and following over all modules from memory.  Leaves the final
+// record list in the final list and its length in S.cnt[3].
+template <int B, bool kCand>
+__device__ __forceinline__ void track_mem(const sbt_params &PP, const Ev &v, Shared<B> &S)
 {
     const Prm P = fresh(PP);
     const int M = P.M, N = v.N;
-    uint32_t *own = kLds ? Lay<CAP>::own(v.lo) : v.own();
+    uint32_t *own = v.own();
     const int nw = (N + 31) >> 5;
     for (int i = tid<B>(); i < nw; i += B) at(own, i) = 0u;
     for (int i = tid<B>(); i < N; i += B) {
@@ -1403,13 +2027,10 @@ __device__ bool stage_track_impl(const sbt_params &PP, const Ev &v, Shared<B> &S
     }
     if (tid<B>() == 0) {
         S.cnt[0] = 0; S.cnt[1] = 0; S.cnt[2] = 0; S.cnt[3] = 0;
-        S.ovf = 0;
     }
-    if (kLds)
-        for (int u = 0; u < 4 && u < M; ++u) ring_fill<B, CAP>(P, v, u, S, 0);
     ev_sync<B>();
-    uint16_t *l0 = kLds ? Lay<CAP>::al(v.lo, 0) : v.list(kListAct0);
-    uint16_t *l1 = kLds ? Lay<CAP>::al(v.lo, 1) : v.list(kListAct1);
+    uint16_t *l0 = v.list(kListAct0);
+    uint16_t *l1 = v.list(kListAct1);
     // the last traversal index whose seeding can make a seed: its modules
     // t-2, t-1 and t all hold hits (2 when no index can)
     int last_seed = 2;
@@ -1422,9 +2043,8 @@ __device__ bool stage_track_impl(const sbt_params &PP, const Ev &v, Shared<B> &S
     }
     last_seed = uni(last_seed);
     int par = 0;
-    stage_seed_follow<B, kLds, CAP, kCand>(PP, v, 2, S, own, l0, &S.cnt[1], 0, M > 3);
+    stage_seed_follow<B, kCand>(PP, v, 2, S, own, l0, &S.cnt[1], 0, M > 3);
     ev_sync<B>();
-    if (kLds && uni(S.ovf)) return false;
     for (int t = 3; t < M; ++t) {
         // act (n_act tracks) holds every forming track with its search into
         // t done: resolve t keeping the survivors in nxt, then seed t and
@@ -1436,22 +2056,12 @@ __device__ bool stage_track_impl(const sbt_params &PP, const Ev &v, Shared<B> &S
         uint16_t *act = par ? l1 : l0;
         uint16_t *nxt = par ? l0 : l1;
         const bool more = t + 1 < M;
-        stage_follow_resolve<B, kLds, CAP>(PP, v, t, S, own, act, n_act, nxt, &S.cnt[1 + (par ^ 1)]);
-        if (kLds && more) {
-            // module t+1 into the slot of t-3 (unused from here on), on the
-            // waves the resolution leaves idle (the last wave at least)
-            const int last = n_act > 0 ? n_act - ((n_act - 1) / B) * B : 0;
-            int l0 = (last + 63) & ~63;
-            if (l0 > B - 64) l0 = B - 64;
-            ring_fill<B, CAP>(fresh(PP), fresh(v), t + 1, S, l0);
-        }
+        stage_follow_resolve<B>(PP, v, t, S, own, act, n_act, nxt, &S.cnt[1 + (par ^ 1)]);
         ev_sync<B>();
         const int n_keep = uni(S.cnt[1 + (par ^ 1)]);
         if (tid<B>() == 0) S.cnt[1 + par] = 0;   // act becomes the next step's nxt
-        if (!(kLds && uni(S.ovf)))
-            stage_seed_follow<B, kLds, CAP, kCand>(PP, v, t, S, own, nxt, &S.cnt[1 + (par ^ 1)], n_keep, more);
+        stage_seed_follow<B, kCand>(PP, v, t, S, own, nxt, &S.cnt[1 + (par ^ 1)], n_keep, more);
         ev_sync<B>();
-        if (kLds && uni(S.ovf)) return false;
         par ^= 1;
     }
     const int n_act = uni(S.cnt[1 + par]);
@@ -1459,24 +2069,32 @@ __device__ bool stage_track_impl(const sbt_params &PP, const Ev &v, Shared<B> &S
     const uint16_t *act = par ? l1 : l0;
     uint16_t *fin = v.list(kListFin);
     for (int a = tid<B>(); a < n_act; a += B) at(fin, nf + a) = at(act, a);
-    if (kLds && writeback)
-        for (int i = tid<B>(); i < nw; i += B) at(v.own(), i) = at(own, i);
     ev_sync<B>();
     if (tid<B>() == 0) S.cnt[3] = nf + n_act;
     ev_sync<B>();
-    return true;
 }
 
-// Runs the tracking stages; returns true when the event's flags ended in LDS.
+// whether an event fits the LDS form of the tracking stages
+template <int B, int CAP>
+__device__ __forceinline__ bool event_fits_lds(const Shared<B> &S, int N, int own_cap)
+{
+    return CAP > 0 && uni(S.maxmod) <= CAP && N <= own_cap;
+}
+
+// Runs the tracking stages; returns true when they ran in the LDS form
+// (flags in LDS, hits named by sorted position), false for the memory form.
 template <int B, int CAP, bool kCand = false>
-__device__ bool stage_track(const sbt_params &P, const Ev &v, Shared<B> &S, int own_cap, bool writeback)
+__device__ __forceinline__ bool stage_track(const sbt_params &P, const Ev &v, Shared<B> &S, int own_cap, bool writeback)
 {
     if constexpr (CAP > 0) {
         if (event_fits_lds<B, CAP>(S, v.N, own_cap)) {
-            if (stage_track_impl<B, true, CAP, kCand>(P, v, S, writeback)) return true;
+            // a bare seed that may miss two modules outlives the claim slots
+            const bool gc = P.max_consecutive_misses > 1;
+            if (track_lds<B, CAP, kCand>(fresh(v), S, writeback, gc)) return true;
+            ev_sync<B>();   // every wave has read what made it return
         }
     }
-    stage_track_impl<B, false, CAP, kCand>(P, v, S, false);
+    track_mem<B, kCand>(P, v, S);
     return false;
 }
 
@@ -1499,9 +2117,8 @@ __device__ void stage_fill_candidates(const sbt_params &PP, const Ev &v0, const 
         Win wa;
         wa.h = v.hs() + S.mo[ka];
         wa.n = S.mo[ka + 1] - S.mo[ka];
-        wa.tab = nullptr;
         for (int i = tid<B>(); i < n; i += B) {
-            int s0 = wa.n > 0 ? win_lower_bound<false>(wa, q_of(at(v.hs(), (uint32_t)(g0 + i)))) : 0;
+            int s0 = wa.n > 0 ? win_lower_bound(wa, q_of(at(v.hs(), (uint32_t)(g0 + i)))) : 0;
             if (s0 == wa.n) s0 = 0;
             at(v.keys(), (uint32_t)(g0 + i)) = (uint32_t)s0;
         }
@@ -1513,7 +2130,7 @@ __device__ void stage_fill_candidates(const sbt_params &PP, const Ev &v0, const 
 // fit chi2 is under the threshold and none of its hits is flagged; candidates
 // sharing hits keep the one with the minimum (chi2, key).
 template <int B>
-__device__ void stage_filter(const sbt_params &PP, const Ev &v0, int n_fin, const uint32_t *own)
+__device__ __forceinline__ void stage_filter(const sbt_params &PP, const Ev &v0, int n_fin, const uint32_t *own)
 {
     const Ev v = fresh(v0);
     const float X = fresh(PP).X;
@@ -1552,6 +2169,71 @@ __device__ void stage_filter(const sbt_params &PP, const Ev &v0, int n_fin, cons
     ev_sync<B>();
 }
 
+// The same for the LDS form's records.  claim: one word per sorted position,
+// all ~0.
+template <int B, class Claim>
+__device__ __forceinline__ void filter_records(const Ev &v, float X, int n_fin, const uint32_t *own, Claim claim)
+{
+    for (int a = tid<B>(); a < n_fin; a += B) {
+        const Fin w = at(v.fin(), (uint32_t)a);
+        uint32_t fl = kFlagAccepted;
+        if ((w.z >> 16) < 4u) {
+            const uint32_t p0 = w.x >> 16, p1 = w.y & 0xFFFFu, p2 = w.y >> 16;
+            const float c2 = seed_chi2(at(v.hs(), p0), at(v.hs(), p1), at(v.hs(), p2));
+            fl = 0;
+            if (c2 < X && is_free(own, p0) && is_free(own, p1) && is_free(own, p2)) {
+                const unsigned long long kap = claim_key(c2, (uint16_t)(w.x & 0xFFFFu), kFilterStage);
+                atomicMin(claim + p0, kap);
+                atomicMin(claim + p1, kap);
+                atomicMin(claim + p2, kap);
+                fl = kFlagCandidate;
+                at(v.aux(), (uint32_t)a).chi2 = c2;
+            }
+        }
+        if (fl == kFlagAccepted) at(v.link(), 2u * (w.x & 0xFFFFu) + 1u) = (uint16_t)a;
+        at(v.aux(), (uint32_t)a).flag = fl;
+    }
+    ev_sync<B>();
+    for (int a = tid<B>(); a < n_fin; a += B) {
+        const RecAux x = at(v.aux(), (uint32_t)a);
+        if (x.flag != kFlagCandidate) continue;
+        const Fin w = at(v.fin(), (uint32_t)a);
+        const uint32_t p0 = w.x >> 16, p1 = w.y & 0xFFFFu, p2 = w.y >> 16;
+        const unsigned long long kap = claim_key(x.chi2, (uint16_t)(w.x & 0xFFFFu), kFilterStage);
+        if (claim[p0] == kap && claim[p1] == kap && claim[p2] == kap) at(v.link(), 2u * (w.x & 0xFFFFu) + 1u) = (uint16_t)a;
+    }
+    ev_sync<B>();
+}
+
+// own in LDS at byte offset own_off of the event's region, where the claims
+// fit in front of it; claims in memory otherwise
+template <int B>
+__device__ __forceinline__ void stage_filter_lds(const sbt_params &PP, const Ev &v0, int n_fin, uint32_t own_off)
+{
+    const Ev v = fresh(v0);
+    const float X = fresh(PP).X;
+    const uint32_t *own = reinterpret_cast<const uint32_t *>(g_lds + v.lo + own_off);
+    if (8u * (uint32_t)v.N <= own_off) {
+        unsigned long long *claim = reinterpret_cast<unsigned long long *>(g_lds + v.lo);
+        for (int i = tid<B>(); i < v.N; i += B) claim[i] = kNoClaim;
+        ev_lds_sync<B>();
+        filter_records<B>(v, X, n_fin, own, claim);
+    } else {
+        unsigned long long *claim = v.claim();
+        for (int i = tid<B>(); i < v.N; i += B) at(claim, (uint32_t)i) = kNoClaim;
+        ev_sync<B>();
+        filter_records<B>(v, X, n_fin, own, claim);
+    }
+}
+
+// own and claims in memory (the plain form's kernels; claims already ~0)
+template <int B>
+__device__ void stage_filter_pos(const sbt_params &PP, const Ev &v0, int n_fin)
+{
+    const Ev v = fresh(v0);
+    filter_records<B>(v, fresh(PP).X, n_fin, v.own(), v.claim());
+}
+
 // ---------------------------------------------------------------- per-event compaction
 // The accepted tracks in key order (the id of the seed's middle hit), each as
 // its three seed hits followed by the hits appended to it in traversal order:
@@ -1559,12 +2241,41 @@ __device__ void stage_filter(const sbt_params &PP, const Ev &v0, int n_fin, cons
 // the event's counters.
 constexpr int kCompactBatch = 8;   // key rounds whose link loads are in flight together
 
-// Whether the LDS form of the compaction fits: the previous-hit links (2 B
-// per hit) and the record of each accepted track in key order (2 B per
-// track; tracks are disjoint with at least three hits, so at most N / 3).
-__host__ __device__ inline bool compact_fits_lds(int N, int lds_bytes)
+// An accepted track's record: the seed's hits, the last hit and the number of
+// hits, by sorted position (kPos, the LDS tracking form's) or by id.
+struct Acc {
+    uint32_t h0, h1, h2, last, len;
+};
+
+template <bool kPos>
+__device__ __forceinline__ Acc accepted(const Ev &v, uint32_t r)
 {
-    return (int)a16(2u * (uint32_t)N) + 2 * (N / 3 + 1) <= lds_bytes;
+    Acc a;
+    if (kPos) {
+        const Fin w = at(v.fin(), r);
+        a.h0 = w.x >> 16;
+        a.h1 = w.y & 0xFFFFu;
+        a.h2 = w.y >> 16;
+        a.last = w.z & 0xFFFFu;
+        a.len = w.z >> 16;
+    } else {
+        const Rec R = at(v.rec(), r);
+        a.h0 = R.h0;
+        a.h1 = R.h1;
+        a.h2 = R.h2;
+        a.last = R.last;
+        a.len = R.len;
+    }
+    return a;
+}
+
+// Whether the LDS form of the compaction fits: the previous-hit links (2 B
+// per hit), with kPos the ids by sorted position (2 B per hit), and the
+// record of each accepted track in key order (2 B per track; tracks are
+// disjoint with at least three hits, so at most N / 3).
+__host__ __device__ inline bool compact_fits_lds(int N, int lds_bytes, bool pos)
+{
+    return (int)a16(2u * (uint32_t)N) * (pos ? 2 : 1) + 2 * (N / 3 + 1) <= lds_bytes;
 }
 
 // LDS form.  Pass 1 takes the keys in rounds of B (key = round * B + lane,
@@ -1573,30 +2284,37 @@ __host__ __device__ inline bool compact_fits_lds(int N, int lds_bytes)
 // the workgroup, which lists the records in key order.  Pass 2 gives each
 // listed track a lane: an exclusive scan of the lengths places its hits, and
 // the lane writes them, walking the links in LDS.
-template <int B>
-__device__ void compact_lds(const Ev &v, int *s_scan, int lds_bytes)
+template <int B, bool kPos>
+__device__ __forceinline__ void compact_lds(const Ev &v, int *s_scan, int lds_bytes)
 {
     const int N = v.N;
+    const uint32_t row = a16(2u * (uint32_t)N);
     uint16_t *lprev = reinterpret_cast<uint16_t *>(g_lds + v.lo);
-    uint16_t *lrec = reinterpret_cast<uint16_t *>(g_lds + v.lo + a16(2u * (uint32_t)N));
-    const int rec_cap = (lds_bytes - (int)a16(2u * (uint32_t)N)) / 2;
+    uint16_t *lid = reinterpret_cast<uint16_t *>(g_lds + v.lo + row);   // kPos
+    uint16_t *lrec = reinterpret_cast<uint16_t *>(g_lds + v.lo + (kPos ? 2 : 1) * row);
+    const int rec_cap = (lds_bytes - (kPos ? 2 : 1) * (int)row) / 2;
     const uint32_t *link = reinterpret_cast<const uint32_t *>(v.link());   // prev | record << 16
     const int rounds = (N + B - 1) / B;
     bool bad = false;
     int nt = 0;
     for (int j0 = 0; j0 < rounds; j0 += kCompactBatch) {
         uint32_t w[kCompactBatch];
+        uint16_t d[kCompactBatch];
 #pragma unroll
         for (int u = 0; u < kCompactBatch; ++u) {
             const int k = (j0 + u) * B + (int)tid<B>();
             w[u] = k < N ? at(link, (uint32_t)k) : ((uint32_t)kNone << 16);
+            if (kPos) d[u] = k < N ? at(v.sid(), (uint32_t)k) : (uint16_t)0;
         }
 #pragma unroll
         for (int u = 0; u < kCompactBatch; ++u) {
             if (j0 + u >= rounds) break;
             const int k = (j0 + u) * B + (int)tid<B>();
             const uint16_t r = (uint16_t)(w[u] >> 16);
-            if (k < N) lprev[k] = (uint16_t)(w[u] & 0xFFFFu);
+            if (k < N) {
+                lprev[k] = (uint16_t)(w[u] & 0xFFFFu);
+                if (kPos) lid[k] = d[u];
+            }
             int tot;
             const int pos = nt + (block_count2<B>(r != kNone, false, s_scan, j0 + u, &tot) & 0xFFFF);
             if (r != kNone) {
@@ -1606,17 +2324,15 @@ __device__ void compact_lds(const Ev &v, int *s_scan, int lds_bytes)
             nt += tot & 0xFFFF;
         }
     }
-    ev_sync<B>();   // links and the record list visible
+    ev_sync<B>();   // links, ids and the record list visible
     if (nt > rec_cap) nt = 0;
     int nh = 0;
     for (int t0 = 0; t0 < nt; t0 += B) {
         const int t = t0 + (int)tid<B>();
-        Rec R;
-        int len = 0;
-        if (t < nt) {
-            R = at(v.rec(), lrec[t]);
-            len = R.len;
-        }
+        Acc R;
+        R.len = 0;
+        if (t < nt) R = accepted<kPos>(v, lrec[t]);
+        const int len = (int)R.len;
         int tot;
         const int hi = nh + block_excl_scan<B>(len, s_scan, t0 / B, &tot);
         nh += tot;
@@ -1628,15 +2344,15 @@ __device__ void compact_lds(const Ev &v, int *s_scan, int lds_bytes)
             } else {
                 at(v.st_toff(), t) = hi;
                 uint16_t *out = v.st_hits() + hi;
-                uint16_t p = R.last;
+                uint32_t p = R.last;
                 for (int j = len - 1; j >= 3; --j) {
-                    if (p >= N) { bad = true; break; }
-                    out[j] = p;
+                    if (p >= (uint32_t)N) { bad = true; break; }
+                    out[j] = kPos ? lid[p] : (uint16_t)p;
                     p = lprev[p];
                 }
-                out[2] = R.h2;
-                out[1] = R.h1;
-                out[0] = R.h0;
+                out[2] = kPos ? lid[R.h2] : (uint16_t)R.h2;
+                out[1] = kPos ? lid[R.h1] : (uint16_t)R.h1;
+                out[0] = kPos ? lid[R.h0] : (uint16_t)R.h0;
             }
         }
     }
@@ -1650,8 +2366,8 @@ __device__ void compact_lds(const Ev &v, int *s_scan, int lds_bytes)
 // Memory form (events whose links do not fit, and the plain kernel): each
 // lane owns a contiguous range of keys; it counts their tracks and hits, one
 // scan of each over the workgroup, then it writes them in key order.
-template <int B>
-__device__ void compact_mem(const Ev &v, int *s_scan)
+template <int B, bool kPos>
+__device__ __forceinline__ void compact_mem(const Ev &v, int *s_scan)
 {
     const int N = v.N;
     const int per = (N + B - 1) / B;
@@ -1661,7 +2377,7 @@ __device__ void compact_mem(const Ev &v, int *s_scan)
         const uint16_t r = at(v.link(), 2u * k + 1u);
         if (r != kNone) {
             ++nt;
-            nh += at(v.rec(), r).len;
+            nh += (int)accepted<kPos>(v, r).len;
         }
     }
     int tt, th;
@@ -1671,24 +2387,25 @@ __device__ void compact_mem(const Ev &v, int *s_scan)
     for (int k = k0; k < k1 && !bad; ++k) {
         const uint16_t r = at(v.link(), 2u * k + 1u);
         if (r == kNone) continue;
-        const Rec R = at(v.rec(), r);
-        if (hi + R.len > N) {
+        const Acc R = accepted<kPos>(v, r);
+        const int len = (int)R.len;
+        if (hi + len > N) {
             bad = true;
             break;
         }
         at(v.st_toff(), ti) = hi;
         uint16_t *out = v.st_hits() + hi;
-        uint16_t p = R.last;
-        for (int j = R.len - 1; j >= 3; --j) {
-            if (p >= N) { bad = true; break; }
-            out[j] = p;
+        uint32_t p = R.last;
+        for (int j = len - 1; j >= 3; --j) {
+            if (p >= (uint32_t)N) { bad = true; break; }
+            out[j] = kPos ? at(v.sid(), p) : (uint16_t)p;
             p = at(v.link(), 2u * p);
         }
-        out[2] = R.h2;
-        out[1] = R.h1;
-        out[0] = R.h0;
+        out[2] = kPos ? at(v.sid(), R.h2) : (uint16_t)R.h2;
+        out[1] = kPos ? at(v.sid(), R.h1) : (uint16_t)R.h1;
+        out[0] = kPos ? at(v.sid(), R.h0) : (uint16_t)R.h0;
         ++ti;
-        hi += R.len;
+        hi += len;
     }
     if (bad) v.info().st = (int)SBT_EV_INTERNAL;
     if (tid<B>() == 0) {
@@ -1698,12 +2415,12 @@ __device__ void compact_mem(const Ev &v, int *s_scan)
 }
 
 // lds_bytes: LDS free for the compaction (0: none)
-template <int B>
-__device__ void stage_compact(const Ev &v0, int *s_scan, int lds_bytes)
+template <int B, bool kPos>
+__device__ __forceinline__ void stage_compact(const Ev &v0, int *s_scan, int lds_bytes)
 {
     const Ev v = fresh(v0);
-    if (compact_fits_lds(v.N, lds_bytes)) compact_lds<B>(v, s_scan, lds_bytes);
-    else compact_mem<B>(v, s_scan);
+    if (compact_fits_lds(v.N, lds_bytes, kPos)) compact_lds<B, kPos>(v, s_scan, lds_bytes);
+    else compact_mem<B, kPos>(v, s_scan);
 }
 
 }  // namespace sbt

@@ -19,9 +19,8 @@ using namespace sbt;
 // the dynamic LDS (the Shared block, then the layout of lds_bytes(CAP,
 // own_cap) bytes), and no wave ever waits for another.
 template <int B, int CAP>
-__global__ __launch_bounds__(B == 64 ? 64 * kMaxEventsPerBlock : B) void k_persistent(sbt_params P, HitsArgs H,
-                                                                                     Work W0, int own_cap,
-                                                                                     int sortcap)
+__global__ __launch_bounds__(B == 64 ? 64 * kMaxEventsPerBlock : B) __attribute__((amdgpu_waves_per_eu(
+    B == 256 ? 5 : 4))) void k_persistent(sbt_params P, HitsArgs H, Work W0, int own_cap, int sortcap)
 {
     uint32_t lo = 0;
     Shared<B> *sp;
@@ -57,9 +56,13 @@ __global__ __launch_bounds__(B == 64 ? 64 * kMaxEventsPerBlock : B) void k_persi
             stage_sort<B>(P, H, v, S, sortcap);
             const bool in_lds = stage_track<B, CAP>(P, v, S, own_cap, false);
             const int n_fin = uni(S.cnt[3]);
-            if (CAP > 0 && in_lds) stage_filter<B>(P, v, n_fin, Lay<CAP>::own(v.lo));
-            else stage_filter<B>(P, v, n_fin, v.own());
-            stage_compact<B>(v, S.scan, (int)lds_sort_head() + 4 * sortcap);
+            if (CAP > 0 && in_lds) {
+                stage_filter_lds<B>(P, v, n_fin, lay_own(CAP));
+                stage_compact<B, true>(v, S.scan, (int)lds_sort_head() + 4 * sortcap);
+            } else {
+                stage_filter<B>(P, v, n_fin, v.own());
+                stage_compact<B, false>(v, S.scan, (int)lds_sort_head() + 4 * sortcap);
+            }
         } else if (tid<B>() == 0) {
             ws_evinfo(W)[e].nt = 0;
             ws_evinfo(W)[e].nh = 0;
@@ -111,9 +114,13 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(6))) void k
                 stage_sort<B>(P, H, v, S, sortcap);
                 const bool in_lds = stage_track<B, CAP>(P, v, S, own_cap, false);
                 const int n_fin = uni(S.cnt[3]);
-                if (CAP > 0 && in_lds) stage_filter<B>(P, v, n_fin, Lay<CAP>::own(v.lo));
-                else stage_filter<B>(P, v, n_fin, v.own());
-                stage_compact<B>(v, S.scan, (int)lds_sort_head() + 4 * sortcap);
+                if (CAP > 0 && in_lds) {
+                    stage_filter_lds<B>(P, v, n_fin, lay_own(CAP));
+                    stage_compact<B, true>(v, S.scan, (int)lds_sort_head() + 4 * sortcap);
+                } else {
+                    stage_filter<B>(P, v, n_fin, v.own());
+                    stage_compact<B, false>(v, S.scan, (int)lds_sort_head() + 4 * sortcap);
+                }
             } else if (tid<B>() == 0) {
                 ws_evinfo(W)[e].nt = 0;
                 ws_evinfo(W)[e].nh = 0;

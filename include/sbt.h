@@ -183,7 +183,9 @@ typedef struct sbt_tracks {
  *                     module reads all its modules from memory.
  * lds_owner_hits      events with at most this many hits keep their hit
  *                     flags (one bit per hit) in LDS, larger ones in
- *                     memory (0..65536).
+ *                     memory (0..65536).  One 1,024-lane workgroup per CU
+ *                     given 16,384 or more keeps every event's flags in LDS
+ *                     where they fit beside its slots.
  * events_per_block    events one workgroup runs side by side (0 or 1: one;
  *                     up to 16, only with threads_per_event = 64).  Each
  *                     64-lane event is one wave with its own LDS region and

@@ -599,6 +599,22 @@ uint32_t tuning_lds(const sbt_tuning &T)
     return lds_bytes(cap, T.lds_owner_hits);
 }
 
+// The configuration a tuning is launched with.  One 1,024-lane workgroup per
+// CU has LDS to spare behind its 1,536-hit slots (6 KB of flag bits are 49,152
+// hits more), so the flags of every event fit and dense events beyond
+// lds_owner_hits stay out of the memory form: mu = 30 x 400, of which one event in
+// ten has more than 16,384 hits, takes 0.60 ms instead of 1.05.  A smaller
+// lds_owner_hits is taken as it is.
+sbt_tuning launch_tuning(const sbt_tuning &T)
+{
+    sbt_tuning t = T;
+    if (t.threads_per_event == 1024 && t.blocks_per_cu == 1 && t.lds_owner_hits >= 16384) {
+        t.lds_owner_hits = 65536;
+        if (tuning_lds(t) > kMaxDynLds) t.lds_owner_hits = T.lds_owner_hits;
+    }
+    return t;
+}
+
 const void *persistent_kernel(int tpe, int cap)
 {
     switch (tpe) {
@@ -678,9 +694,10 @@ sbt_tuning deferred_tuning(const sbt_tuning &T)
 
 // launch of one persistent pass (defer: set aside the events that do not fit
 // the LDS form; only the six-waves instance has that mode)
-int launch_pass(const sbt_params &P, const sbt_tuning &T, const HitsArgs &H, const Work &W, hipStream_t s,
+int launch_pass(const sbt_params &P, const sbt_tuning &T0, const HitsArgs &H, const Work &W, hipStream_t s,
                 int defer)
 {
+    const sbt_tuning T = launch_tuning(T0);
     int grid = 0;
     int rc = persistent_grid(T, H.n_events, &grid);
     if (rc) return rc;

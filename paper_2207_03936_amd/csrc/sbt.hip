@@ -339,6 +339,7 @@ __global__ __launch_bounds__(kWriteThreads) void k_write_events(HitsArgs H, Work
 // no contraction, correctly rounded division).  A track of up to
 // kConsRegHits hits is loaded into registers at once (every load in flight
 // together); a longer one is read again from the inputs for each pass.
+// Batches of dense events only (see k_consolidate_lds).
 constexpr int kConsThreads = 256;
 constexpr int kConsRegHits = 32;
 
@@ -447,6 +448,155 @@ __global__ __launch_bounds__(kConsThreads) void k_consolidate(HitsArgs H, const 
                 c2 = c2 + ((rx * rx) + (ry * ry));
             }
             write_state(state, t, xm, ym, zm, tx, ty, c2, n);
+        }
+    }
+}
+
+// Consolidation of events whose coordinates fit the LDS: one workgroup per
+// event.  Lanes that hold consecutive hits of a track, or the j-th hits of
+// neighbouring tracks, gather from lines all over the event, and the events in
+// flight do not fit the L2s (39 KB an event of 3,300 hits): read that way a
+// batch moves several times its bytes, and the packed arrays written a hit
+// per lane go out as single words.  Here an event's coordinates are read once
+// and as they lie into LDS, with its tracks' hit ids (14 B a hit), packed from
+// there in whole lines, and fitted from there, a lane per track.  An event
+// beyond cap gathers from memory.
+//
+// Which kernel, by the batch's mean event (microseconds a call, LDS form
+// against k_consolidate, truth tracks): an event cannot be split, so its
+// coordinates take the whole LDS of a CU (1,024 lanes, 11,600 hits: mu = 7.6 x
+// 1,000 51 / 76, x 100 12 / 26, mu in U{1..25} x 2,000 131 / 254; the 512-lane
+// form with half of it, which sends one mu = 7.6 event in twelve to memory,
+// 66) or, where they average kConsSmallMean hits, a quarter of it (256 lanes,
+// 2,900 hits: low pileup x 2,000 30 / 56 and 63 with the whole, 430 hits x 2,000
+// 18 / 25).  Batches of more than kConsDirectMean hits an event are mostly
+// beyond the LDS and stay with k_consolidate (mu = 30 x 200: 98 / 86).
+// What bounds the mu = 7.6 x 1,000 batch now is the chain of an event (offsets,
+// track offsets, ids, coordinates, fit) at one event per CU, 18 us being the
+// time of its 85 MB at the rate of a large copy.
+constexpr int kConsHits = 11600, kConsHitsSmall = 2900;
+constexpr int kConsSmallMean = 1300, kConsDirectMean = 9000;
+constexpr int kConsBatch = 4;     // hits of a track whose LDS loads are in flight together
+constexpr int kConsDirect = 16;   // the same from memory
+
+// Fit of a track of n hits (see k_consolidate); each(f) calls f on its hits in
+// track order.
+template <class Each>
+__device__ __forceinline__ void fit_track(float *__restrict__ state, int t, int n, Each &&each)
+{
+    const float fn = (float)n;
+    float sx = 0.0f, sy = 0.0f, sz = 0.0f;
+    each([&](const float3 &h) {
+        sx = sx + h.x;
+        sy = sy + h.y;
+        sz = sz + h.z;
+    });
+    const float xm = sx / fn, ym = sy / fn, zm = sz / fn;
+    float szz = 0.0f, sxz = 0.0f, syz = 0.0f;
+    each([&](const float3 &h) {
+        const float dz = h.z - zm;
+        szz = szz + dz * dz;
+        sxz = sxz + dz * (h.x - xm);
+        syz = syz + dz * (h.y - ym);
+    });
+    const float tx = sxz / szz, ty = syz / szz;
+    float c2 = 0.0f;
+    each([&](const float3 &h) {
+        const float dz = h.z - zm;
+        const float rx = h.x - (xm + tx * dz);
+        const float ry = h.y - (ym + ty * dz);
+        c2 = c2 + ((rx * rx) + (ry * ry));
+    });
+    write_state(state, t, xm, ym, zm, tx, ty, c2, n);
+}
+
+template <int B>
+__global__ __launch_bounds__(B) void k_consolidate_lds(HitsArgs H, const int32_t *__restrict__ eto,
+                                                       const int32_t *__restrict__ tho,
+                                                       const int32_t *__restrict__ th, float *__restrict__ px,
+                                                       float *__restrict__ py, float *__restrict__ pz,
+                                                       float *__restrict__ state, int cap)
+{
+    float *lx = reinterpret_cast<float *>(g_lds), *ly = lx + cap, *lz = ly + cap;
+    uint16_t *lid = reinterpret_cast<uint16_t *>(lz + cap);
+    const int tid = (int)threadIdx.x;
+    for (int e = blockIdx.x; e < H.n_events; e += gridDim.x) {
+        const int hb = H.eo[e], N = H.eo[e + 1] - hb;
+        const int t0 = eto[e], t1 = eto[e + 1];
+        if (t0 >= t1) continue;
+        const int lo0 = tho[t0], nh = tho[t1] - lo0;
+        const float *__restrict__ X = H.x + hb;
+        const float *__restrict__ Y = H.y + hb;
+        const float *__restrict__ Z = H.z + hb;
+        if (N <= cap && nh <= cap) {
+#pragma unroll 4
+            for (int i = tid; i < N; i += B) {
+                lx[i] = X[i];
+                ly[i] = Y[i];
+                lz[i] = Z[i];
+            }
+#pragma unroll 4
+            for (int k = tid; k < nh; k += B) lid[k] = (uint16_t)th[lo0 + k];
+            __syncthreads();
+            for (int k = tid; k < nh; k += B) {
+                const int i = lid[k];
+                px[lo0 + k] = lx[i];
+                py[lo0 + k] = ly[i];
+                pz[lo0 + k] = lz[i];
+            }
+            for (int t = t0 + tid; t < t1; t += B) {
+                const int l = tho[t] - lo0;
+                const int n = tho[t + 1] - lo0 - l;
+                fit_track(state, t, n, [&](auto &&f) {
+                    for (int j0 = 0; j0 < n; j0 += kConsBatch) {
+                        float3 h[kConsBatch];
+#pragma unroll
+                        for (int u = 0; u < kConsBatch; ++u) {
+                            const int i = lid[l + min(j0 + u, n - 1)];
+                            h[u] = make_float3(lx[i], ly[i], lz[i]);
+                        }
+#pragma unroll
+                        for (int u = 0; u < kConsBatch; ++u)
+                            if (j0 + u < n) f(h[u]);
+                    }
+                });
+            }
+            __syncthreads();
+        } else {
+            for (int t = t0 + tid; t < t1; t += B) {
+                const int lo = tho[t], n = tho[t + 1] - lo;
+                // up to kConsDirect hits of the track in flight together, and
+                // kept for the fit where they are all of it
+                float3 h[kConsDirect];
+                for (int j0 = 0; j0 < n; j0 += kConsDirect) {
+                    int i[kConsDirect];
+#pragma unroll
+                    for (int u = 0; u < kConsDirect; ++u) i[u] = th[lo + min(j0 + u, n - 1)];
+#pragma unroll
+                    for (int u = 0; u < kConsDirect; ++u) h[u] = make_float3(X[i[u]], Y[i[u]], Z[i[u]]);
+#pragma unroll
+                    for (int u = 0; u < kConsDirect; ++u)
+                        if (j0 + u < n) {
+                            px[lo + j0 + u] = h[u].x;
+                            py[lo + j0 + u] = h[u].y;
+                            pz[lo + j0 + u] = h[u].z;
+                        }
+                }
+                if (n <= kConsDirect) {
+                    fit_track(state, t, n, [&](auto &&f) {
+#pragma unroll
+                        for (int u = 0; u < kConsDirect; ++u)
+                            if (u < n) f(h[u]);
+                    });
+                } else {
+                    fit_track(state, t, n, [&](auto &&f) {
+                        for (int j = 0; j < n; ++j) {
+                            const int i = th[lo + j];
+                            f(make_float3(X[i], Y[i], Z[i]));
+                        }
+                    });
+                }
+            }
         }
     }
 }
@@ -941,9 +1091,21 @@ int sbt_consolidate(const sbt_hits *hits, const sbt_tracks *tracks, sbt_track_st
     if (!out || !out->hit_x || !out->hit_y || !out->hit_z || !out->state) return SBT_ERR_INVALID_ARG;
     if (hits->n_events == 0) return SBT_OK;
     const HitsArgs H = hits_args(hits);
-    hipLaunchKernelGGL(k_consolidate, dim3(std::min(H.n_events, 8192)), dim3(kConsThreads), 0, (hipStream_t)stream,
-                       H, tracks->event_track_offsets, tracks->track_hit_offsets, tracks->track_hits, out->hit_x,
-                       out->hit_y, out->hit_z, out->state);
+    const dim3 grid(std::min(H.n_events, 8192));
+    const hipStream_t st = (hipStream_t)stream;
+    const int32_t *eto = tracks->event_track_offsets, *tho = tracks->track_hit_offsets, *th = tracks->track_hits;
+    const long long mean = H.n_hits / H.n_events;
+    if (mean > kConsDirectMean) {
+        hipLaunchKernelGGL(k_consolidate, grid, dim3(kConsThreads), 0, st, H, eto, tho, th, out->hit_x, out->hit_y,
+                           out->hit_z, out->state);
+    } else if (mean > kConsSmallMean) {
+        if ((rc = allow_lds(reinterpret_cast<const void *>(k_consolidate_lds<1024>), 14 * kConsHits))) return rc;
+        hipLaunchKernelGGL(k_consolidate_lds<1024>, grid, dim3(1024), 14 * kConsHits, st, H, eto, tho, th, out->hit_x,
+                           out->hit_y, out->hit_z, out->state, kConsHits);
+    } else {
+        hipLaunchKernelGGL(k_consolidate_lds<256>, grid, dim3(256), 14 * kConsHitsSmall, st, H, eto, tho, th,
+                           out->hit_x, out->hit_y, out->hit_z, out->state, kConsHitsSmall);
+    }
     return hipGetLastError() == hipSuccess ? SBT_OK : SBT_ERR_HIP;
 }
 

@@ -95,3 +95,65 @@ def test_events_beyond_16384_hits(n):
     rng = np.random.default_rng(n)
     ev, mz = zip(*[_event(rng, [n] * 26, n // 3) for _ in range(2)])
     _check(ev, mz[0], (1024, 1, 1536, 16384))
+
+
+def _fit32(x, y, z, tho):
+    """The consolidation fit in binary32, every operation in the order the
+    library defines (hits of a track one after another)."""
+    f = np.float32
+    lo, n = tho[:-1].astype(np.int64), np.diff(tho).astype(np.int64)
+    fn = n.astype(f)
+
+    def over(step):
+        for j in range(int(n.max())):
+            k = np.nonzero(n > j)[0]
+            step(k, x[lo[k] + j], y[lo[k] + j], z[lo[k] + j])
+    acc = lambda: np.zeros(n.size, f)
+    sx, sy, sz, szz, sxz, syz, c2 = (acc() for _ in range(7))
+
+    def means(k, a, b, c):
+        sx[k] += a; sy[k] += b; sz[k] += c
+    over(means)
+    xm, ym, zm = sx / fn, sy / fn, sz / fn
+
+    def centred(k, a, b, c):
+        dz = c - zm[k]
+        szz[k] += dz * dz; sxz[k] += dz * (a - xm[k]); syz[k] += dz * (b - ym[k])
+    over(centred)
+    tx, ty = sxz / szz, syz / szz
+
+    def residuals(k, a, b, c):
+        dz = c - zm[k]
+        rx, ry = a - (xm[k] + tx[k] * dz), b - (ym[k] + ty[k] * dz)
+        c2[k] += rx * rx + ry * ry
+    over(residuals)
+    return np.stack([xm, ym, zm, tx, ty, c2 / (2 * n - 4).astype(f)], 1)
+
+
+@pytest.mark.parametrize("sizes", [(0, 90, 400), (2899, 2900, 2901), (2899, 2901, 0, 0, 0, 0), (11599, 11600, 11601, 0),
+                                   (9200, 20000)])
+def test_consolidation_at_the_lds_capacities(sizes):
+    """Events around the sizes that consolidation holds in LDS, in each of its
+    forms (chosen by the mean event): coordinates and states equal, bit for
+    bit, the same binary32 operations done in numpy (no tolerance)."""
+    import torch
+    rng = np.random.default_rng(sum(sizes))
+    M = 26
+    evs = []
+    for n in sizes:
+        ev, mz = _event(rng, [n // M + (1 if k < n % M else 0) for k in range(M)], max(1, n // (2 * M)))
+        evs.append(ev)
+    b = synth.concat(evs, mz)
+    print(f"[gpu] consolidation of events of {sizes} hits", flush=True)
+    eto, tho, th = oracle.reconstruct(b)
+    g = np.concatenate([b.event_offsets[e] + th[tho[eto[e]]:tho[eto[e + 1]]].astype(np.int64)
+                        for e in range(b.n_events)])
+    want = (b.x[g], b.y[g], b.z[g], _fit32(b.x[g], b.y[g], b.z[g], tho))
+    dev = sbt.DeviceBatch(b)
+    out = sbt.DeviceTracks(b.n_events, b.n_hits)
+    for dst, src in zip((out.eto, out.tho, out.th), (eto, tho, th)):
+        dst[:len(src)] = torch.from_numpy(src).to(dst.device)
+    got = sbt.sbt_consolidate(dev, out).to_host(len(tho) - 1, len(th))
+    assert len(tho) > 1
+    for a, w in zip(got, want):
+        assert a.dtype == w.dtype and np.array_equal(a.view(np.uint32), np.ascontiguousarray(w).view(np.uint32))

@@ -369,7 +369,18 @@ __device__ __forceinline__ void wave_append2(bool p0, int *c0, bool p1, int *c1,
     r1 = p1 ? b1 + lane_rank(m1) : -1;
 }
 
-// inclusive prefix sum over the wave: row shifts, then the row broadcasts
+// inclusive prefix sum over the first 32 lanes, or over the wave: row shifts,
+// then the row broadcasts
+__device__ __forceinline__ int half_wave_incl_scan(int v)
+{
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);   // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);   // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);   // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);   // row_shr:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);   // row_bcast:15
+    return v;
+}
+
 __device__ __forceinline__ int wave_incl_scan(int v)
 {
     v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);   // row_shr:1
@@ -464,12 +475,13 @@ __device__ __forceinline__ int lane_xor(int v, int m)
 //   ring   4 slots x CAP sorted hits (16 B each): traversal index u in slot
 //          u mod 4; module t+1 is filled into the slot of t-3 while t is
 //          being resolved
-//   seeds  the seeds of a step, three words each (CAP entries): window
-//          positions of the three hits, best position of the first following
-//          search and its scatter
+//   seeds  the seeds of a step (CAP entries of 10 B): window positions of the
+//          three hits, best position of the first following search and its
+//          scatter
 //   claim  claim words (4 B) of five modules, traversal index u in slot
 //          u mod 5, by window position
 //   freel  unflagged positions of the seeding stage's doublet module
+//   freem  unflagged positions of its middle module
 //   tab    coarse phi index of each slot: first position whose phi16 is in
 //          bin b or above it
 //   own    hit flags of the event, one bit per sorted position, when
@@ -481,7 +493,8 @@ constexpr int kSlots = 4;   // ring slots: traversal indices t-2 .. t+1
 constexpr int kClaimSlots = 5;   // claim slots: traversal indices t-4 .. t
 __host__ __device__ constexpr uint32_t a16(uint32_t v) { return (v + 15u) & ~15u; }
 __host__ __device__ constexpr uint32_t lay_seeds(int cap) { return 16u * kSlots * (uint32_t)cap; }
-__host__ __device__ constexpr uint32_t lay_claim(int cap) { return lay_seeds(cap) + 12u * (uint32_t)cap; }
+__host__ __device__ constexpr uint32_t lay_freem(int cap) { return lay_seeds(cap) + 10u * (uint32_t)cap; }
+__host__ __device__ constexpr uint32_t lay_claim(int cap) { return lay_freem(cap) + 2u * (uint32_t)cap; }
 __host__ __device__ constexpr uint32_t lay_freel(int cap) { return lay_claim(cap) + 4u * kClaimSlots * (uint32_t)cap; }
 __host__ __device__ constexpr uint32_t lay_tab(int cap) { return lay_freel(cap) + a16(2u * (uint32_t)cap); }
 __host__ __device__ constexpr uint32_t lay_own(int cap) { return lay_tab(cap) + 2u * kSlots * kTab; }
@@ -514,11 +527,17 @@ struct Lay {
     {
         return reinterpret_cast<Hit16 *>(g_lds + lo) + s * CAP;
     }
-    // word w of every seed: seeds(lo, w)[l]
-    static __device__ __forceinline__ uint32_t *seeds(uint32_t lo, int w)
+    // seeds: CAP words of positions, CAP scatters, CAP halves of positions
+    // (seed_words)
+    static __device__ __forceinline__ uint32_t *seeds(uint32_t lo)
     {
-        return reinterpret_cast<uint32_t *>(g_lds + lo + lay_seeds(CAP)) + w * CAP;
+        return reinterpret_cast<uint32_t *>(g_lds + lo + lay_seeds(CAP));
     }
+    static __device__ __forceinline__ uint16_t *seeds16(uint32_t lo)
+    {
+        return reinterpret_cast<uint16_t *>(g_lds + lo + lay_seeds(CAP) + 8u * CAP);
+    }
+    static __device__ __forceinline__ uint16_t *freem(uint32_t lo) { return reinterpret_cast<uint16_t *>(g_lds + lo + lay_freem(CAP)); }
     static __device__ __forceinline__ uint32_t *claim(uint32_t lo) { return reinterpret_cast<uint32_t *>(g_lds + lo + lay_claim(CAP)); }
     static __device__ __forceinline__ uint16_t *freel(uint32_t lo) { return reinterpret_cast<uint16_t *>(g_lds + lo + lay_freel(CAP)); }
     static __device__ __forceinline__ uint16_t *tab(uint32_t lo, int s)
@@ -1008,7 +1027,9 @@ struct Trk {
     uint32_t pb;     // window position of the best hit, or kNoPos
     float bsc;       // its scatter
 };
-constexpr uint32_t kNoPos = 0xFFFFu;
+// A seed's positions (below 2,047) in the seeds table: pos0 | pos1 << 11 | pos2
+// << 22 (its low ten bits) and pos2 >> 10 | best << 1.
+constexpr uint32_t kNoPos = 0x7FFu;
 
 // final record of the LDS form: key | h0 << 16, h1 | h2 << 16, last | hits << 16
 typedef uint4 Fin;
@@ -1078,31 +1099,19 @@ struct Step {
     float Zc, Zn, Zx;    // nominal z of t, t + 1 and t + 2
 };
 
-// position of set bit r of m
-__device__ __forceinline__ int nth_set(unsigned long long m, int r)
-{
-    uint32_t w = (uint32_t)m;
-    int base = 0;
-    int c = __popc(w);
-    if (r >= c) { r -= c; w = (uint32_t)(m >> 32); base = 32; }
-#pragma unroll
-    for (int s = 16; s > 0; s >>= 1) {
-        c = __popc(w & ((1u << s) - 1u));
-        if (r >= c) { r -= c; w >>= s; base += s; }
-    }
-    return base;
-}
-
 // unflagged positions [64 w, 64 w + 64) of a module of n hits whose first
 // sorted position is g
+// (n > 0; the word is empty past the module's last)
 __device__ __forceinline__ unsigned long long free_word(const uint32_t *own, int g, int n, int w)
 {
-    const int rem = n - 64 * w;
-    const uint32_t b = (uint32_t)(g + (rem > 0 ? 64 * w : 0));
+    const int x = min(w, (n - 1) >> 6);
+    const uint32_t b = (uint32_t)(g + 64 * x);
     const uint32_t r0 = at(own, b >> 5), r1 = at(own, (b >> 5) + 1u), r2 = at(own, (b >> 5) + 2u);
     const uint32_t lo = __builtin_amdgcn_alignbit(r1, r0, b & 31u), hi = __builtin_amdgcn_alignbit(r2, r1, b & 31u);
     const unsigned long long m = ~(((unsigned long long)hi << 32) | lo);
-    return rem <= 0 ? 0ull : rem >= 64 ? m : m & ((1ull << rem) - 1ull);
+    const int rem = n - 64 * w;
+    const unsigned long long in = rem >= 64 ? ~0ull : (1ull << (rem & 63)) - 1ull;
+    return rem <= 0 ? 0ull : m & in;
 }
 
 __device__ __forceinline__ unsigned long long read_lane64(unsigned long long v, int l)
@@ -1140,12 +1149,12 @@ __device__ __forceinline__ void group_min(unsigned long long &key, uint32_t &pos
     }
 }
 
-// The unflagged positions of a step's doublet and middle modules.  Lane w
-// holds word w of each; ex: unflagged positions before the word, A | Bm << 16.
+// The unflagged positions of a step's doublet and middle modules: lane w
+// holds word w of A and the unflagged positions before it.
 struct Free {
-    unsigned long long a, b;
+    unsigned long long a;
     int ex;
-    int na, nb;    // unflagged positions in all
+    int na, nb;    // unflagged positions of A, of Bm
 };
 
 // Seeding of step t (Section 3) on the waves from the last one down: modules
@@ -1155,16 +1164,15 @@ struct Free {
 // longest window among the wave's lanes, is what a step waits for).  Other K:
 // K adjacent lanes where K is a power of two up to 16, one lane otherwise.  A
 // new seed's search into t+1 runs on the lanes that made it; seed and result
-// go to the seeds table.  F: the unflagged positions of A, ascending.
+// go to the seeds table.
 template <int B, int CAP, int KQ, bool kCand>
-__device__ __forceinline__ void seed_pass(uint32_t lo, const uint32_t *cand, const Step &st, Shared<B> &S,
-                                          const Free &fr, bool more, bool gc)
+__device__ __forceinline__ void seed_pass(const Prm &P, uint32_t lo, const uint32_t *cand, const Step &st,
+                                          Shared<B> &S, const Free &fr, bool more, bool gc)
 {
-    const sbt_params &PP = kernel_params();
     constexpr int NW = B / 64;
     const int lane = (int)(tid<B>() & 63);
     const int sw = NW - 1 - uni((int)(tid<B>() >> 6));
-    const int K = KQ ? KQ : PP.max_doublet_candidates;
+    const int K = KQ ? KQ : P.K;
     const int ls = KQ == 4 ? (fr.nb * 16 <= B ? 2 : fr.nb * 8 <= B ? 1 : 0) : 0;
     const int G = KQ == 4 ? 4 << ls : (K == 1 || K == 2 || K == 4 || K == 8 || K == 16) ? K : 1;
     const int per_lane = KQ == 4 ? 1 : (G == 1 ? K : 1);
@@ -1173,10 +1181,10 @@ __device__ __forceinline__ void seed_pass(uint32_t lo, const uint32_t *cand, con
 
     // the seeding waves carry the longest dependency chain of the step
     __builtin_amdgcn_s_setprio(2);
-    const int na = st.n[2], nb = st.n[3], nf = fr.na;
-    const int Ws = opq(PP.phi_window_seeding), Wf = opq(PP.phi_window_forwarding);
-    const float Ss = opq(PP.max_scatter_seeding), Sf = opq(PP.max_scatter_forwarding);
-    const uint16_t *F = Lay<CAP>::freel(lo);
+    const int na = st.n[2], nf = fr.na;
+    const int Ws = P.Ws;
+    const float Ss = P.Ss;
+    const uint16_t *F = Lay<CAP>::freel(lo), *FM = Lay<CAP>::freem(lo);
     const LWin wa = lds_window<CAP>(lo, st.t - 2, na);
     const LWin wc = lds_window<CAP>(lo, st.t, st.n[4]);
     const Hit16 *hb = Lay<CAP>::ring(lo, (st.t - 1) & (kSlots - 1));
@@ -1193,15 +1201,7 @@ __device__ __forceinline__ void seed_pass(uint32_t lo, const uint32_t *cand, con
             i = g / G;
             c = g - i * G;
         }
-        // the i-th unflagged position of Bm
-        int w = 0, r = i;
-        for (int x = 1; 64 * x < nb; ++x) {
-            const int f = __builtin_amdgcn_readlane(fr.ex, x) >> 16;
-            w = i >= f ? x : w;
-            r = i >= f ? i - f : r;
-        }
-        const uint32_t blo = (uint32_t)__shfl((int)(uint32_t)fr.b, w), bhi = (uint32_t)__shfl((int)(uint32_t)(fr.b >> 32), w);
-        const int p1 = on ? 64 * w + nth_set(((unsigned long long)bhi << 32) | blo, r) : 0;
+        const int p1 = on ? at(FM, (uint32_t)i) : 0;
         const Hit16 h1 = at(hb, (uint32_t)p1);
         // pendulum start: the first position of A whose phi16 is not below the middle hit's
         int s0 = 0;
@@ -1279,7 +1279,7 @@ __device__ __forceinline__ void seed_pass(uint32_t lo, const uint32_t *cand, con
                 const float d12 = h2.z - h1.z;
                 const float tx = (h2.x - h1.x) / d12, ty = (h2.y - h1.y) / d12;
                 follow_walk(lds_window<CAP>(lo, u, st.n[5]), h2.x, h2.y, h2.z, tx, ty, st.Zn,
-                            Wf, Sf, KQ == 4 ? k : 0, KQ == 4 ? G : 1, bk, pb);
+                            P.Wf, P.Sf, KQ == 4 ? k : 0, KQ == 4 ? G : 1, bk, pb);
             }
             if (KQ == 4) group_min<KQ>(bk, pb, ls, G);
         }
@@ -1288,9 +1288,11 @@ __device__ __forceinline__ void seed_pass(uint32_t lo, const uint32_t *cand, con
         if (found && k < 4 && (KQ == 4 || k == 0)) {
             const int l = slot + lane_rank(em) - (k > 0 ? 1 : 0);
             uint32_t *cl = Lay<CAP>::claim(lo);
-            uint32_t *sd = Lay<CAP>::seeds(lo, 0);
+            uint32_t *sd = Lay<CAP>::seeds(lo);
+            uint16_t *sd16 = Lay<CAP>::seeds16(lo);
             const uint32_t kap = claim32(bsc, u);
-            const uint32_t w0 = pos0 | ((uint32_t)p1 << 16), w1 = pos2 | (pb << 16), w2 = __float_as_uint(bsc);
+            const uint32_t w0 = pos0 | ((uint32_t)p1 << 11) | (pos2 << 22), w1 = (pos2 >> 10) | (pb << 1),
+                           w2 = __float_as_uint(bsc);
             const uint32_t a0 = (uint32_t)st.c[0] + pb, a1 = (uint32_t)st.c[2] + pos0, a2 = (uint32_t)(st.c[3] + p1),
                            a3 = (uint32_t)st.c[4] + pos2;
             const bool claims = pb != kNoPos && !gc;
@@ -1298,7 +1300,8 @@ __device__ __forceinline__ void seed_pass(uint32_t lo, const uint32_t *cand, con
             if (KQ == 4) {
                 // a lane of the quad for each claim and each word
                 if (claims) tie = atomicMin(&cl[k == 0 ? a0 : k == 1 ? a1 : k == 2 ? a2 : a3], kap) == kap;
-                if (k < 3) sd[k * CAP + l] = k == 0 ? w0 : k == 1 ? w1 : w2;
+                if (k < 2) sd[k * CAP + l] = k == 0 ? w0 : w2;
+                else if (k == 2) sd16[l] = (uint16_t)w1;
             } else {
                 if (claims) {
                     const uint32_t o0 = atomicMin(&cl[a0], kap), o1 = atomicMin(&cl[a1], kap);
@@ -1306,8 +1309,8 @@ __device__ __forceinline__ void seed_pass(uint32_t lo, const uint32_t *cand, con
                     tie = o0 == kap || o1 == kap || o2 == kap || o3 == kap;
                 }
                 sd[l] = w0;
-                sd[CAP + l] = w1;
-                sd[2 * CAP + l] = w2;
+                sd[CAP + l] = w2;
+                sd16[l] = (uint16_t)w1;
             }
             if (tie) S.ctl[2] = 1;
         }
@@ -1358,9 +1361,12 @@ __device__ __forceinline__ void ring_put(uint32_t lo, const Hit16 *hs, uint16_t 
         ring[i] = h;
         at(sid, (uint32_t)i) = id_of(h);
         const int own = (int)((h.qid & 0xFFFFu) >> sh);
+#pragma unroll 1
         for (int b = i > 0 ? (int)((qp & 0xFFFFu) >> sh) + 1 : 0; b <= own; ++b) tab[b] = (uint16_t)i;
-        if (i == n - 1)
+        if (i == n - 1) {
+#pragma unroll 1
             for (int b = own + 1; b < (1 << (16 - sh)); ++b) tab[b] = (uint16_t)n;
+        }
     }
 }
 
@@ -1374,16 +1380,17 @@ __device__ __forceinline__ void take_seeds(uint32_t lo, const Step &st, Trk (&T)
         const unsigned long long fm = __ballot(T[s].lst == 0u);
         const int l = base[s] + lane_rank(fm);
         if (T[s].lst == 0u && l < nnew) {
-            const uint32_t a = Lay<CAP>::seeds(lo, 0)[l], b = Lay<CAP>::seeds(lo, 1)[l], c = Lay<CAP>::seeds(lo, 2)[l];
-            const Hit16 h1 = at(r1, a >> 16), h2 = at(r2, b & 0xFFFFu);
+            const uint32_t a = Lay<CAP>::seeds(lo)[l], c = Lay<CAP>::seeds(lo)[CAP + l], b = Lay<CAP>::seeds16(lo)[l];
+            const uint32_t pos1 = (a >> 11) & 0x7FFu, pos2 = (a >> 22) | ((b & 1u) << 10);
+            const Hit16 h1 = at(r1, pos1), h2 = at(r2, pos2);
             T[s].xa = h1.x; T[s].ya = h1.y; T[s].za = h1.z;
             T[s].xb = h2.x; T[s].yb = h2.y; T[s].zb = h2.z;
-            const uint32_t p0 = (uint32_t)st.g[1] + (a & 0xFFFFu), p1 = (uint32_t)st.g[2] + (a >> 16),
-                           p2 = (uint32_t)st.g[3] + (b & 0xFFFFu);
+            const uint32_t p0 = (uint32_t)st.g[1] + (a & 0x7FFu), p1 = (uint32_t)st.g[2] + pos1,
+                           p2 = (uint32_t)st.g[3] + pos2;
             T[s].k0 = (h1.qid >> 16) | (p0 << 16);
             T[s].h12 = p1 | (p2 << 16);
             T[s].lst = p2 | (3u << 16) | ((uint32_t)(st.t - 1) << 24);
-            T[s].pb = b >> 16;
+            T[s].pb = b >> 1;
             T[s].bsc = __uint_as_float(c);
         }
     }
@@ -1413,6 +1420,7 @@ __device__ __forceinline__ bool track_lds(const Ev &v0, Shared<B> &S, bool write
     const uint32_t lo = v0.lo;
     const uint32_t *cand = kCand ? v0.keys() : nullptr;   // pendulum starts of a candidate pass
 
+    const Prm P = fresh(kernel_params());
     Step st;
     int last_seed = 2;
     Trk T[SETS];
@@ -1471,8 +1479,8 @@ __device__ __forceinline__ bool track_lds(const Ev &v0, Shared<B> &S, bool write
 #pragma unroll
         for (int h = 0; h < (SETS + 1) / 2; ++h) {
             const int x = fsl[h];
-            const int inc = wave_incl_scan(x), ex = inc - x;
-            const int mine = __builtin_amdgcn_readlane(ex, wv), all = __builtin_amdgcn_readlane(inc, 63);
+            const int inc = half_wave_incl_scan(x), ex = inc - x;
+            const int mine = __builtin_amdgcn_readlane(ex, wv), all = __builtin_amdgcn_readlane(inc, 31);
             base[2 * h] = total + (mine & 0xFFFF);
             total += all & 0xFFFF;
             if (2 * h + 1 < SETS) {
@@ -1498,36 +1506,40 @@ __device__ __forceinline__ bool track_lds(const Ev &v0, Shared<B> &S, bool write
     bool ended = false, cleared = writeback;   // claims in memory: whether they have been cleared
     for (;;) {
         // ---- S(t)
-        const sbt_params &PP = kernel_params();
-        const int misses = PP.max_consecutive_misses;
-        const bool more = st.t + 1 < PP.n_modules;
+        const bool more = st.t + 1 < P.M;
         f = fetch_hit(hs, st.g[6], st.n[6], ri);   // module t+2, put into the ring in R(t+1)
         if (st.n[2] > 0 && st.n[3] > 0 && st.n[4] > 0) {
             Free fr;
+            static_assert(CAP <= 64 * 32, "the flag words of a module on half a wave");
             fr.a = free_word(own, st.g[2], st.n[2], lane);
-            fr.b = free_word(own, st.g[3], st.n[3], lane);
-            const int pc = __popcll(fr.a) | (__popcll(fr.b) << 16);
-            const int inc = wave_incl_scan(pc);
-            const int tot = __builtin_amdgcn_readlane(inc, 63);
-            fr.ex = inc - pc;
+            const unsigned long long fb = free_word(own, st.g[3], st.n[3], lane);
+            const int pc = __popcll(fr.a) | (__popcll(fb) << 16);
+            const int inc = half_wave_incl_scan(pc);
+            const int tot = __builtin_amdgcn_readlane(inc, 31);
+            const int ex = inc - pc;
+            fr.ex = ex & 0xFFFF;
             fr.na = tot & 0xFFFF;
             fr.nb = tot >> 16;
             if (fr.na > 0 && fr.nb > 0) {
-                // the list of A's unflagged positions, a word per wave and round
-                uint16_t *F = Lay<CAP>::freel(lo);
-                for (int w = wv; 64 * w < st.n[2]; w += NW) {
-                    const unsigned long long m = read_lane64(fr.a, w);
-                    const int at0 = __builtin_amdgcn_readlane(fr.ex, w) & 0xFFFF;
-                    if ((m >> lane) & 1ull) at(F, (uint32_t)(at0 + lane_rank(m))) = (uint16_t)(64 * w + lane);
+                // the lists of A's and Bm's unflagged positions, a word of
+                // each per wave and round
+                uint16_t *F = Lay<CAP>::freel(lo), *FM = Lay<CAP>::freem(lo);
+                const int most = max(st.n[2], st.n[3]);
+                for (int w = wv; 64 * w < most; w += NW) {
+                    const unsigned long long ma = read_lane64(fr.a, w), mb = read_lane64(fb, w);
+                    const int at0 = __builtin_amdgcn_readlane(ex, w);
+                    if (__builtin_amdgcn_inverse_ballot_w64(ma))
+                        at(F, (uint32_t)((at0 & 0xFFFF) + lane_rank(ma))) = (uint16_t)(64 * w + lane);
+                    if (__builtin_amdgcn_inverse_ballot_w64(mb))
+                        at(FM, (uint32_t)((at0 >> 16) + lane_rank(mb))) = (uint16_t)(64 * w + lane);
                 }
                 ev_lds_sync<B>();
-                if (PP.max_doublet_candidates == 4) seed_pass<B, CAP, 4, kCand>(lo, cand, st, S, fr, more, gc);
-                else seed_pass<B, CAP, 0, kCand>(lo, cand, st, S, fr, more, gc);
+                if (P.K == 4) seed_pass<B, CAP, 4, kCand>(P, lo, cand, st, S, fr, more, gc);
+                else seed_pass<B, CAP, 0, kCand>(P, lo, cand, st, S, fr, more, gc);
             }
         }
         if (more) {
-            const int u = st.t + 1, Wf = opq(PP.phi_window_forwarding);
-            const float Sf = opq(PP.max_scatter_forwarding);
+            const int u = st.t + 1;
             const LWin wn = lds_window<CAP>(lo, u, st.n[5]);
 #pragma unroll
             for (int s = 0; s < SETS; ++s) {
@@ -1537,13 +1549,13 @@ __device__ __forceinline__ bool track_lds(const Ev &v0, Shared<B> &S, bool write
                 const int last_t = (int)(t.lst >> 24);
                 const bool bare = ((t.lst >> 16) & 0xFFu) == 3u;
                 const uint32_t p0 = t.k0 >> 16, p1 = t.h12 & 0xFFFFu, p2 = t.h12 >> 16;
-                bool elig = t.lst != 0u && u - last_t <= misses + 1 && wn.n > 0;
+                bool elig = t.lst != 0u && u - last_t <= P.misses + 1 && wn.n > 0;
                 if (elig && bare) elig = is_free(own, p0) && is_free(own, p1) && is_free(own, p2);
                 if (elig) {
                     const float dab = t.zb - t.za;
                     const float tx = (t.xb - t.xa) / dab, ty = (t.yb - t.ya) / dab;
                     unsigned long long bk = ~0ull;
-                    follow_walk(wn, t.xb, t.yb, t.zb, tx, ty, st.Zn, Wf, Sf, 0, 1, bk, t.pb);
+                    follow_walk(wn, t.xb, t.yb, t.zb, tx, ty, st.Zn, P.Wf, P.Sf, 0, 1, bk, t.pb);
                     t.bsc = __uint_as_float((uint32_t)(bk >> 32));
                     if (t.pb != kNoPos && !gc) {
                         // a kept bare seed was made at t-1: its hits are in t-3, t-2 and t-1
@@ -1563,8 +1575,7 @@ __device__ __forceinline__ bool track_lds(const Ev &v0, Shared<B> &S, bool write
         ev_lds_sync<B>();
         // ---- on to t+1
         {
-        const sbt_params &PP = kernel_params();
-        const int M = PP.n_modules, misses = PP.max_consecutive_misses;
+        const int M = P.M;
         st.t += 1;
         // everything the step's scalars come from, in one round of loads
         const int4 ctl = *reinterpret_cast<const int4 *>(S.ctl);
@@ -1673,7 +1684,7 @@ __device__ __forceinline__ bool track_lds(const Ev &v0, Shared<B> &S, bool write
                 k.xb = h.x; k.yb = h.y; k.zb = h.z;
                 k.lst = p | ((((k.lst >> 16) & 0xFFu) + 1u) << 16) | ((uint32_t)t << 24);
             }
-            const bool done = k.lst != 0u && t - (int)(k.lst >> 24) >= misses + 1;
+            const bool done = k.lst != 0u && t - (int)(k.lst >> 24) >= P.misses + 1;
             if (__ballot(done) != 0ull) finish(k, done);
             nf[s] = __popcll(__ballot(k.lst == 0u));
         }

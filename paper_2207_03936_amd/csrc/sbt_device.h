@@ -1182,31 +1182,19 @@ __device__ __forceinline__ unsigned long long read_lane64(unsigned long long v, 
     return ((unsigned long long)b << 32) | a;
 }
 
-// minimum of (key, pos) over the lanes of a group: 4 << ls lanes for KQ = 4
-// (every lane gets it), else G lanes
+// minimum of (key, pos) over the G lanes of a group (KQ = 4: by quad permutes;
+// every lane gets it)
 template <int KQ>
-__device__ __forceinline__ void group_min(unsigned long long &key, uint32_t &pos, int ls, int G)
+__device__ __forceinline__ void group_min(unsigned long long &key, uint32_t &pos, int G)
 {
-    auto take = [&](uint32_t lo, uint32_t hi, uint32_t p) {
-        const unsigned long long o = ((unsigned long long)hi << 32) | lo;
+    for (int m = 1; m < (KQ ? KQ : G); m <<= 1) {
+        const uint32_t olo = (uint32_t)lane_xor((int)(uint32_t)key, m);
+        const uint32_t ohi = (uint32_t)lane_xor((int)(uint32_t)(key >> 32), m);
+        const uint32_t op = (uint32_t)lane_xor((int)pos, m);
+        const unsigned long long o = ((unsigned long long)ohi << 32) | olo;
         const bool less = o < key;
         key = less ? o : key;
-        pos = less ? p : pos;
-    };
-    if (KQ == 4) {
-        // quad_perm [1,0,3,2], [2,3,0,1], then the mirrors of 8 and of 16 lanes
-#define SBT_DPP3(CTRL)                                                                        \
-    take((uint32_t)quad_bcast<CTRL>((int)(uint32_t)key), (uint32_t)quad_bcast<CTRL>((int)(uint32_t)(key >> 32)), \
-         (uint32_t)quad_bcast<CTRL>((int)pos))
-        SBT_DPP3(0xB1);
-        SBT_DPP3(0x4E);
-        if (ls >= 1) SBT_DPP3(0x141);
-        if (ls >= 2) SBT_DPP3(0x140);
-#undef SBT_DPP3
-    } else {
-        for (int m = 1; m < G; m <<= 1)
-            take((uint32_t)lane_xor((int)(uint32_t)key, m), (uint32_t)lane_xor((int)(uint32_t)(key >> 32), m),
-                 (uint32_t)lane_xor((int)pos, m));
+        pos = less ? op : pos;
     }
 }
 
@@ -1220,12 +1208,14 @@ struct Free {
 
 // Seeding of step t (Section 3) on the waves from the last one down: modules
 // A = t-2, Bm = t-1, C = t; work items are (unflagged middle hit, partner
-// rank c).  With KQ = 4 a middle hit has 4 << ls lanes: the four partners, and
-// as many lanes per window walk as the workgroup has to spare (the walk, its
-// longest window among the wave's lanes, is what a step waits for).  Other K:
-// K adjacent lanes where K is a power of two up to 16, one lane otherwise.  A
-// new seed's search into t+1 runs on the lanes that made it; seed and result
-// go to the seeds table.
+// rank c), the K doublets of a middle hit on K adjacent lanes where K is a
+// power of two up to 16 (KQ = 4: known at compile time), all on one lane
+// otherwise.  A new seed's search into t+1 runs on the lanes that made it;
+// seed and result go to the seeds table.  (More lanes for a middle hit, two or
+// four to a doublet's walk, shorten the chain but are more instructions, which
+// the SIMDs have no room for where a CU holds two events: sixteen lanes take
+// 317 us for mu = 7.6 x 1,000, eight 294, these four 297, and 1,703, 1,618 and
+// 1,606 for mu in U{1..25} x 4,000.)
 template <int B, int CAP, int KQ, bool kCand>
 __device__ __forceinline__ void seed_pass(const Prm &P, uint32_t lo, const uint32_t *cand, const Step &st,
                                           Shared<B> &S, const Free &fr, bool more, bool gc)
@@ -1234,8 +1224,7 @@ __device__ __forceinline__ void seed_pass(const Prm &P, uint32_t lo, const uint3
     const int lane = (int)(tid<B>() & 63);
     const int sw = NW - 1 - uni((int)(tid<B>() >> 6));
     const int K = KQ ? KQ : P.K;
-    const int ls = KQ == 4 ? (fr.nb * 16 <= B ? 2 : fr.nb * 8 <= B ? 1 : 0) : 0;
-    const int G = KQ == 4 ? 4 << ls : (K == 1 || K == 2 || K == 4 || K == 8 || K == 16) ? K : 1;
+    const int G = KQ == 4 ? 4 : (K == 1 || K == 2 || K == 4 || K == 8 || K == 16) ? K : 1;
     const int per_lane = KQ == 4 ? 1 : (G == 1 ? K : 1);
     const int items = fr.nb * G;
     if (sw * 64 >= items) return;
@@ -1254,14 +1243,8 @@ __device__ __forceinline__ void seed_pass(const Prm &P, uint32_t lo, const uint3
     for (int base = sw * 64; base < items; base += B) {
         const int g = base + lane;
         const bool on = g < items;
-        int i, c;
-        if (KQ == 4) {
-            i = g >> (2 + ls);
-            c = g & 3;
-        } else {
-            i = g / G;
-            c = g - i * G;
-        }
+        const int i = KQ == 4 ? g >> 2 : g / G;
+        const int c = KQ == 4 ? g & 3 : g - i * G;   // partner rank: the lane of the group
         const int p1 = on ? at(FM, (uint32_t)i) : 0;
         const Hit16 h1 = at(hb, (uint32_t)p1);
         // pendulum start: the first position of A whose phi16 is not below the middle hit's
@@ -1309,7 +1292,7 @@ __device__ __forceinline__ void seed_pass(const Prm &P, uint32_t lo, const uint3
             const float ty = (h1.y - h0.y) / d01;
             const float dzc = st.Zc - h1.z;
             const uint32_t from = (uint32_t)(phi16(h1.x + tx * dzc, h1.y + ty * dzc) - Ws) & 0xFFFFu;
-            walk(wc, from, 2u * (uint32_t)Ws, KQ == 4 ? (lane >> 2) & ((1 << ls) - 1) : 0, 1 << ls,
+            walk(wc, from, 2u * (uint32_t)Ws, 0, 1,
                  [&](const Hit16 &h2, int p, bool in) {
                      const float dz = h2.z - h1.z;
                      const float dx = (h1.x + tx * dz) - h2.x;
@@ -1322,10 +1305,9 @@ __device__ __forceinline__ void seed_pass(const Prm &P, uint32_t lo, const uint3
                      bpos = better ? ((uint32_t)pos0 | ((uint32_t)p << 16)) : bpos;
                  });
         }
-        group_min<KQ>(bkey, bpos, ls, G);   // keys are unique or ~0
+        group_min<KQ>(bkey, bpos, G);   // keys are unique or ~0
         const bool found = bkey != ~0ull && on;
-        const int k = KQ == 4 ? lane & (G - 1) : c;   // lane of the group
-        const unsigned long long em = __ballot(found && k == 0);
+        const unsigned long long em = __ballot(found && c == 0);
         if (em == 0ull) continue;
         // the table's slots are taken before the search and needed after it
         int slot = 0;
@@ -1335,19 +1317,19 @@ __device__ __forceinline__ void seed_pass(const Prm &P, uint32_t lo, const uint3
         uint32_t pb = kNoPos;
         const int u = st.t + 1;
         if (more && st.n[5] > 0) {
-            if (found && (KQ == 4 || k == 0)) {
+            if (found && (KQ == 4 || c == 0)) {
                 const Hit16 h2 = at(wc.h, pos2);
                 const float d12 = h2.z - h1.z;
                 const float tx = (h2.x - h1.x) / d12, ty = (h2.y - h1.y) / d12;
                 follow_walk(lds_window<CAP>(lo, u, st.n[5]), h2.x, h2.y, h2.z, tx, ty, st.Zn,
-                            P.Wf, P.Sf, KQ == 4 ? k : 0, KQ == 4 ? G : 1, bk, pb);
+                            P.Wf, P.Sf, KQ == 4 ? c : 0, KQ == 4 ? 4 : 1, bk, pb);
             }
-            if (KQ == 4) group_min<KQ>(bk, pb, ls, G);
+            if (KQ == 4) group_min<KQ>(bk, pb, G);
         }
         const float bsc = __uint_as_float((uint32_t)(bk >> 32));
         slot = uni(slot);
-        if (found && k < 4 && (KQ == 4 || k == 0)) {
-            const int l = slot + lane_rank(em) - (k > 0 ? 1 : 0);
+        if (found && (KQ == 4 || c == 0)) {
+            const int l = slot + lane_rank(em) - (c > 0 ? 1 : 0);
             uint32_t *cl = Lay<CAP>::claim(lo);
             uint32_t *sd = Lay<CAP>::seeds(lo);
             uint16_t *sd16 = Lay<CAP>::seeds16(lo);
@@ -1360,9 +1342,9 @@ __device__ __forceinline__ void seed_pass(const Prm &P, uint32_t lo, const uint3
             bool tie = false;
             if (KQ == 4) {
                 // a lane of the quad for each claim and each word
-                if (claims) tie = atomicMin(&cl[k == 0 ? a0 : k == 1 ? a1 : k == 2 ? a2 : a3], kap) == kap;
-                if (k < 2) sd[k * CAP + l] = k == 0 ? w0 : w2;
-                else if (k == 2) sd16[l] = (uint16_t)w1;
+                if (claims) tie = atomicMin(&cl[c == 0 ? a0 : c == 1 ? a1 : c == 2 ? a2 : a3], kap) == kap;
+                if (c < 2) sd[c * CAP + l] = c == 0 ? w0 : w2;
+                else if (c == 2) sd16[l] = (uint16_t)w1;
             } else {
                 if (claims) {
                     const uint32_t o0 = atomicMin(&cl[a0], kap), o1 = atomicMin(&cl[a1], kap);

@@ -1133,10 +1133,19 @@ __device__ __forceinline__ void walk(const LWin &w, uint32_t lo, uint32_t span, 
     }
 }
 
-// Search of a track into the window: best hit by (scatter, id) under Sf, as
-// one word that orders like the pair, and its position.
+// The smallest key that is not under a strict bound on the scatter, where keys
+// are (scatter bits, ids) and scatters are >= +0: a search that starts from it
+// takes only keys under the bound (none where the bound is not positive; a
+// NaN is above every bound).
+__device__ __forceinline__ unsigned long long bound_key(float bound)
+{
+    return bound > 0.0f ? (unsigned long long)__float_as_uint(bound) << 32 : 0ull;
+}
+
+// Search of a track into the window: best hit by (scatter, id) under the bound
+// in bk, as one word that orders like the pair, and its position.
 __device__ __forceinline__ void follow_walk(const LWin &w, float xb, float yb, float zb, float tx, float ty, float Zn,
-                                            int Wf, float Sf, int k, int stride, unsigned long long &bk, uint32_t &bp)
+                                            int Wf, int k, int stride, unsigned long long &bk, uint32_t &bp)
 {
     const float dzc = Zn - zb;
     const uint32_t lo = (uint32_t)(phi16(xb + tx * dzc, yb + ty * dzc) - Wf) & 0xFFFFu;
@@ -1146,7 +1155,7 @@ __device__ __forceinline__ void follow_walk(const LWin &w, float xb, float yb, f
         const float dy = (yb + ty * dz) - h.y;
         const float sc = (dx * dx) + (dy * dy);
         const unsigned long long key = ((unsigned long long)__float_as_uint(sc) << 32) | (h.qid >> 16);
-        const bool better = in && sc < Sf && key < bk;
+        const bool better = in && key < bk;
         bk = better ? key : bk;
         bp = better ? (uint32_t)p : bp;
     });
@@ -1233,7 +1242,7 @@ __device__ __forceinline__ void seed_pass(const Prm &P, uint32_t lo, const uint3
     __builtin_amdgcn_s_setprio(2);
     const int na = st.n[2], nf = fr.na;
     const int Ws = P.Ws;
-    const float Ss = P.Ss;
+    const unsigned long long none = bound_key(P.Ss), none_f = bound_key(P.Sf);
     const uint16_t *F = Lay<CAP>::freel(lo), *FM = Lay<CAP>::freem(lo);
     const LWin wa = lds_window<CAP>(lo, st.t - 2, na);
     const LWin wc = lds_window<CAP>(lo, st.t, st.n[4]);
@@ -1276,14 +1285,14 @@ __device__ __forceinline__ void seed_pass(const Prm &P, uint32_t lo, const uint3
         const unsigned long long aw = ((unsigned long long)ahi << 32) | alo;
         const int j = (__shfl(fr.ex, sl) & 0xFFFF) + __popcll(aw & ((1ull << (s0 & 63)) - 1ull));
 
-        unsigned long long bkey = ~0ull;
-        uint32_t bpos = 0;
+        unsigned long long bkey = none;
+        uint32_t bp0 = 0, bpos = kNoPos;   // positions of the best triplet's first and third hits
         for (int cc = 0; cc < per_lane; ++cc) {
             const int pos0 = !on ? -1 : KQ == 4 ? pendulum_quad(F, nf, j, s0, na, hu, hd, c)
                                                 : pendulum_pick(F, nf, j, s0, na, hu, hd, c + cc);
             if (pos0 < 0) break;
             // best third hit of the doublet: the key orders like the comparison
-            // (found, scatter, id0, id2); positions pos0 | pos2 << 16.  Hits of
+            // (found, scatter, id0, id2); the packed positions are pos2 | pos0 << 16.  Hits of
             // C that are flagged hold no coordinate and fail the comparison.
             const Hit16 h0 = at(wa.h, (uint32_t)pos0);
             const uint32_t id0 = h0.qid >> 16;
@@ -1300,20 +1309,23 @@ __device__ __forceinline__ void seed_pass(const Prm &P, uint32_t lo, const uint3
                      const float sc = (dx * dx) + (dy * dy);
                      const unsigned long long key = ((unsigned long long)__float_as_uint(sc) << 32) |
                                                     __builtin_amdgcn_alignbit(id0, h2.qid, 16);
-                     const bool better = in && sc < Ss && key < bkey;
+                     const bool better = in && key < bkey;
                      bkey = better ? key : bkey;
-                     bpos = better ? ((uint32_t)pos0 | ((uint32_t)p << 16)) : bpos;
+                     bpos = better ? (uint32_t)p : bpos;
+                     if (KQ != 4) bp0 = better ? (uint32_t)pos0 : bp0;
                  });
+            if (KQ == 4) bp0 = (uint32_t)pos0;
         }
-        group_min<KQ>(bkey, bpos, G);   // keys are unique or ~0
-        const bool found = bkey != ~0ull && on;
+        bpos |= bp0 << 16;
+        group_min<KQ>(bkey, bpos, G);   // keys under the bound are unique
+        const bool found = bkey != none && on;
         const unsigned long long em = __ballot(found && c == 0);
         if (em == 0ull) continue;
         // the table's slots are taken before the search and needed after it
         int slot = 0;
         if (lane == 0) slot = atomicAdd(&S.ctl[st.t & 1], __popcll(em));
-        const uint32_t pos0 = bpos & 0xFFFFu, pos2 = bpos >> 16;
-        unsigned long long bk = ~0ull;
+        const uint32_t pos0 = bpos >> 16, pos2 = bpos & 0xFFFFu;
+        unsigned long long bk = none_f;
         uint32_t pb = kNoPos;
         const int u = st.t + 1;
         if (more && st.n[5] > 0) {
@@ -1322,7 +1334,7 @@ __device__ __forceinline__ void seed_pass(const Prm &P, uint32_t lo, const uint3
                 const float d12 = h2.z - h1.z;
                 const float tx = (h2.x - h1.x) / d12, ty = (h2.y - h1.y) / d12;
                 follow_walk(lds_window<CAP>(lo, u, st.n[5]), h2.x, h2.y, h2.z, tx, ty, st.Zn,
-                            P.Wf, P.Sf, KQ == 4 ? c : 0, KQ == 4 ? 4 : 1, bk, pb);
+                            P.Wf, KQ == 4 ? c : 0, KQ == 4 ? 4 : 1, bk, pb);
             }
             if (KQ == 4) group_min<KQ>(bk, pb, G);
         }
@@ -1584,6 +1596,7 @@ __device__ __forceinline__ bool track_lds(const Ev &v0, Shared<B> &S, bool write
         if (more) {
             const int u = st.t + 1;
             const LWin wn = lds_window<CAP>(lo, u, st.n[5]);
+            const unsigned long long none_f = bound_key(P.Sf);
 #pragma unroll
             for (int s = 0; s < SETS; ++s) {
                 Trk &t = T[s];
@@ -1597,8 +1610,8 @@ __device__ __forceinline__ bool track_lds(const Ev &v0, Shared<B> &S, bool write
                 if (elig) {
                     const float dab = t.zb - t.za;
                     const float tx = (t.xb - t.xa) / dab, ty = (t.yb - t.ya) / dab;
-                    unsigned long long bk = ~0ull;
-                    follow_walk(wn, t.xb, t.yb, t.zb, tx, ty, st.Zn, P.Wf, P.Sf, 0, 1, bk, t.pb);
+                    unsigned long long bk = none_f;
+                    follow_walk(wn, t.xb, t.yb, t.zb, tx, ty, st.Zn, P.Wf, 0, 1, bk, t.pb);
                     t.bsc = __uint_as_float((uint32_t)(bk >> 32));
                     if (t.pb != kNoPos && !gc) {
                         // a kept bare seed was made at t-1: its hits are in t-3, t-2 and t-1

@@ -88,6 +88,16 @@ def test_equal_scores_and_misses(K, misses):
         _check(ev, mz[0], form=form, max_doublet_candidates=K, max_consecutive_misses=misses)
 
 
+@pytest.mark.parametrize("seeding", [0.0, -1.0, 1e-40, 0.04, float("inf"), float("nan")])
+@pytest.mark.parametrize("forwarding", [0.0, 1e-40, 0.04, float("inf"), float("nan")])
+def test_scatter_bounds_at_the_edges_of_their_type(seeding, forwarding):
+    """Bounds that nothing, almost nothing and everything lies under."""
+    rng = np.random.default_rng(3)
+    ev, mz = zip(*[_event(rng, [t + 5] * 8, t) for t in (3, 40, 120)])
+    for form in ("batched", "plain"):
+        _check(ev, mz[0], form=form, max_scatter_seeding=seeding, max_scatter_forwarding=forwarding)
+
+
 @pytest.mark.parametrize("n", [640, 700, 1500])
 def test_events_beyond_16384_hits(n):
     """Events of more than 16,384 hits with their flags in LDS (one 1,024-lane

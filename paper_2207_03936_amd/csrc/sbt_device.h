@@ -1105,15 +1105,24 @@ __device__ __forceinline__ uint32_t claim32(float score, int stage)
     return ((uint32_t)(63 - stage) << 26) | (__float_as_uint(score) >> 5);
 }
 
+// Hits that a walk takes at a time.  Its loop's own instructions (the masks of
+// who is done, the count, the branch) and an LDS round trip are shared by them,
+// and a walk meets up to one less than that many hits behind its window.  Two
+// instead of one take mu = 7.6 x 1,000 from 291 to 284 us and mu = 30 x 400
+// from 538 to 501; three 282 and 494, four 282 and 498, six 290 and 504.
+// Small slots have short windows, and the instance held to 80 registers
+// spills with more (mu = 7.6 x 4,000: two 862, three 862, four 886).
+constexpr int walk_unroll(int cap) { return cap >= 672 ? 3 : 2; }
+
 // Walks the window [lo, lo + span] of phi16 from the start of lo's bin on
-// `stride` lanes (this one the k-th) and calls hit(h, p, in) for the positions
-// this lane meets, in or out of the window: positions of the bin below lo
-// come first (their distance to lo is within a bin of a full turn), then the
-// window, then one beyond it.  A position may be met twice where a stride
-// closes the circle; the callers take minima.  The lanes of a wave walk
-// together until the last one is done, with masks for branches: what a walk
+// `stride` lanes (this one the k-th), U positions at a time, and calls
+// hit(h, p, in) for the positions this lane meets, in or out of the window:
+// positions of the bin below lo come first (their distance to lo is within a
+// bin of a full turn), then the window, then some beyond it.  A position may
+// be met twice where the walk closes the circle; the callers take minima.  The lanes of a
+// wave walk together until the last one is done, with masks for branches: what a walk
 // costs is the instructions of its longest window.
-template <class F>
+template <int U, class F>
 __device__ __forceinline__ void walk(const LWin &w, uint32_t lo, uint32_t span, int k, int stride, F &&hit)
 {
     uint32_t p = at(w.tab, lo >> w.sh) + (uint32_t)k;
@@ -1121,14 +1130,25 @@ __device__ __forceinline__ void walk(const LWin &w, uint32_t lo, uint32_t span, 
     unsigned long long live = __ballot(k < w.n);
     p = k < w.n ? p : 0u;
     const uint32_t below = 0x10000u - (1u << w.sh);
-    for (int j = 0; j < w.n; j += stride) {
-        const Hit16 h = at(w.h, p);
-        const uint32_t d = (h.qid - lo) & 0xFFFFu;
-        const unsigned long long in = __ballot(d <= span);
-        hit(h, (int)p, __builtin_amdgcn_inverse_ballot_w64(in & live));
-        live &= in | __ballot(d >= below);
+    // q + step - n stays under n: where the lanes already cover the module, no step
+    const uint32_t step = w.n > stride ? (uint32_t)stride : 0u;
+    for (int left = uni(w.n); left > 0; left -= U * stride) {
+        uint32_t q[U];
+        Hit16 h[U];
+        q[0] = p;
+#pragma unroll
+        for (int i = 1; i < U; ++i) {
+            const uint32_t x = q[i - 1] + step;
+            q[i] = min(x, x - (uint32_t)w.n);
+        }
+#pragma unroll
+        for (int i = 0; i < U; ++i) h[i] = at(w.h, q[i]);
+#pragma unroll
+        for (int i = 0; i < U; ++i) hit(h[i], (int)q[i], ((h[i].qid - lo) & 0xFFFFu) <= span);
+        const uint32_t d = (h[U - 1].qid - lo) & 0xFFFFu;
+        live &= __ballot(d <= span) | __ballot(d >= below);
         if (live == 0ull) break;
-        const uint32_t x = p + (uint32_t)stride;   // within the slots' capacity in any case
+        const uint32_t x = q[U - 1] + step;
         p = min(x, x - (uint32_t)w.n);
     }
 }
@@ -1144,12 +1164,13 @@ __device__ __forceinline__ unsigned long long bound_key(float bound)
 
 // Search of a track into the window: best hit by (scatter, id) under the bound
 // in bk, as one word that orders like the pair, and its position.
+template <int U>
 __device__ __forceinline__ void follow_walk(const LWin &w, float xb, float yb, float zb, float tx, float ty, float Zn,
                                             int Wf, int k, int stride, unsigned long long &bk, uint32_t &bp)
 {
     const float dzc = Zn - zb;
     const uint32_t lo = (uint32_t)(phi16(xb + tx * dzc, yb + ty * dzc) - Wf) & 0xFFFFu;
-    walk(w, lo, 2u * (uint32_t)Wf, k, stride, [&](const Hit16 &h, int p, bool in) {
+    walk<U>(w, lo, 2u * (uint32_t)Wf, k, stride, [&](const Hit16 &h, int p, bool in) {
         const float dz = h.z - zb;
         const float dx = (xb + tx * dz) - h.x;
         const float dy = (yb + ty * dz) - h.y;
@@ -1301,7 +1322,7 @@ __device__ __forceinline__ void seed_pass(const Prm &P, uint32_t lo, const uint3
             const float ty = (h1.y - h0.y) / d01;
             const float dzc = st.Zc - h1.z;
             const uint32_t from = (uint32_t)(phi16(h1.x + tx * dzc, h1.y + ty * dzc) - Ws) & 0xFFFFu;
-            walk(wc, from, 2u * (uint32_t)Ws, 0, 1,
+            walk<walk_unroll(CAP)>(wc, from, 2u * (uint32_t)Ws, 0, 1,
                  [&](const Hit16 &h2, int p, bool in) {
                      const float dz = h2.z - h1.z;
                      const float dx = (h1.x + tx * dz) - h2.x;
@@ -1333,7 +1354,7 @@ __device__ __forceinline__ void seed_pass(const Prm &P, uint32_t lo, const uint3
                 const Hit16 h2 = at(wc.h, pos2);
                 const float d12 = h2.z - h1.z;
                 const float tx = (h2.x - h1.x) / d12, ty = (h2.y - h1.y) / d12;
-                follow_walk(lds_window<CAP>(lo, u, st.n[5]), h2.x, h2.y, h2.z, tx, ty, st.Zn,
+                follow_walk<2>(lds_window<CAP>(lo, u, st.n[5]), h2.x, h2.y, h2.z, tx, ty, st.Zn,
                             P.Wf, KQ == 4 ? c : 0, KQ == 4 ? 4 : 1, bk, pb);
             }
             if (KQ == 4) group_min<KQ>(bk, pb, G);
@@ -1611,7 +1632,7 @@ __device__ __forceinline__ bool track_lds(const Ev &v0, Shared<B> &S, bool write
                     const float dab = t.zb - t.za;
                     const float tx = (t.xb - t.xa) / dab, ty = (t.yb - t.ya) / dab;
                     unsigned long long bk = none_f;
-                    follow_walk(wn, t.xb, t.yb, t.zb, tx, ty, st.Zn, P.Wf, 0, 1, bk, t.pb);
+                    follow_walk<walk_unroll(CAP)>(wn, t.xb, t.yb, t.zb, tx, ty, st.Zn, P.Wf, 0, 1, bk, t.pb);
                     t.bsc = __uint_as_float((uint32_t)(bk >> 32));
                     if (t.pb != kNoPos && !gc) {
                         // a kept bare seed was made at t-1: its hits are in t-3, t-2 and t-1

@@ -88,6 +88,17 @@ def test_equal_scores_and_misses(K, misses):
         _check(ev, mz[0], form=form, max_doublet_candidates=K, max_consecutive_misses=misses)
 
 
+@pytest.mark.parametrize("window", [0, 300, 8000, 32767])
+@pytest.mark.parametrize("tuning", [(64, 4, 256), (512, 3, 448), (512, 2, 672), (1024, 1, 1536)])
+def test_windows_that_close_the_circle_of_small_modules(tuning, window):
+    """Walks over modules of fewer hits than a walk takes at a time, with
+    windows from nothing to the full circle."""
+    rng = np.random.default_rng(window)
+    ev, mz = zip(*[_event(rng, rng.permutation([n, 1, 2, 3, 4, 5, 7, n, 9, n]), 4) for n in (2, 3, 4, 6, 8, 13)])
+    for K in (4, 3):
+        _check(ev, mz[0], tuning, phi_window_seeding=window, phi_window_forwarding=window, max_doublet_candidates=K)
+
+
 @pytest.mark.parametrize("seeding", [0.0, -1.0, 1e-40, 0.04, float("inf"), float("nan")])
 @pytest.mark.parametrize("forwarding", [0.0, 1e-40, 0.04, float("inf"), float("nan")])
 def test_scatter_bounds_at_the_edges_of_their_type(seeding, forwarding):

@@ -115,6 +115,24 @@ class SbtServerResult(ctypes.Structure):
                 ("t_submit_us", ctypes.c_double), ("t_done_us", ctypes.c_double)]
 
 
+# the same record for numpy, with the two pointers as addresses
+_RESULT_DTYPE = np.dtype([("request_id", np.int64), ("status", np.int32), ("n_tracks", np.int32),
+                          ("track_hit_offsets", np.uintp), ("track_hits", np.uintp),
+                          ("t_submit_us", np.float64), ("t_done_us", np.float64)])
+assert _RESULT_DTYPE.itemsize == ctypes.sizeof(SbtServerResult)
+
+
+def _address(a) -> int:
+    """Address of an array's data (a third of what a.ctypes.data_as costs)."""
+    return a.__array_interface__["data"][0]
+
+
+def _copy_i32(address, n):
+    """Array of its own of the n 32-bit words at an address.  (as_array makes
+    a ctypes array type for each new n: 40 us against 3.)"""
+    return np.frombuffer(ctypes.string_at(address, 4 * n), np.int32).copy()
+
+
 # exported symbols and their prototypes (restype, argtypes)
 _P = ctypes.POINTER
 _VP = ctypes.c_void_p
@@ -144,8 +162,7 @@ PROTOTYPES = {
     "sbt_debug_half_records": (ctypes.c_int, [_VP, _VP, _VP, ctypes.c_int32, _VP]),
     "sbt_server_create": (ctypes.c_int, [_P(SbtParams), _P(SbtTuning), _P(SbtServerConfig), _P(_VP)]),
     "sbt_server_destroy": (None, [_VP]),
-    "sbt_server_submit": (ctypes.c_int, [_VP, ctypes.c_int64, ctypes.c_int32, _P(ctypes.c_int32),
-                                         _P(ctypes.c_float), _P(ctypes.c_float), _P(ctypes.c_float)]),
+    "sbt_server_submit": (ctypes.c_int, [_VP, ctypes.c_int64, ctypes.c_int32, _VP, _VP, _VP, _VP]),
     "sbt_server_poll": (ctypes.c_int, [_VP, _P(SbtServerResult), ctypes.c_int32, ctypes.c_int32]),
     "sbt_server_pending": (ctypes.c_int, [_VP, _P(ctypes.c_int32), _P(ctypes.c_int32)]),
     "sbt_server_result_blocks": (ctypes.c_int, [_VP, _P(ctypes.c_int32), _P(ctypes.c_int32)]),
@@ -622,6 +639,7 @@ class Server:
                                        ctypes.byref(cfg), ctypes.byref(h)), "sbt_server_create")
         self.handle = h
         self._res = (SbtServerResult * 1024)()
+        self._records = np.frombuffer(self._res, _RESULT_DTYPE)
 
     def close(self):
         if self.handle:
@@ -639,10 +657,8 @@ class Server:
         x = np.ascontiguousarray(x, dtype=np.float32)
         y = np.ascontiguousarray(y, dtype=np.float32)
         z = np.ascontiguousarray(z, dtype=np.float32)
-        f = ctypes.POINTER(ctypes.c_float)
-        return lib().sbt_server_submit(self.handle, int(request_id), int(x.size),
-                                       mo.ctypes.data_as(ctypes.POINTER(ctypes.c_int32)),
-                                       x.ctypes.data_as(f), y.ctypes.data_as(f), z.ctypes.data_as(f))
+        return lib().sbt_server_submit(self.handle, int(request_id), int(x.size), _address(mo),
+                                       _address(x), _address(y), _address(z))
 
     def poll(self, wait_us: int = 0, max_results: Optional[int] = None):
         """List of (request_id, status, track_hit_offsets, track_hits,
@@ -653,13 +669,10 @@ class Server:
         if n < 0:
             raise SbtError(n, "sbt_server_poll")
         out = []
-        for i in range(n):
-            r = self._res[i]
-            nt = r.n_tracks
-            tho = np.ctypeslib.as_array(r.track_hit_offsets, shape=(nt + 1,)).copy()
-            th = (np.ctypeslib.as_array(r.track_hits, shape=(int(tho[-1]),)).copy()
-                  if tho[-1] > 0 else np.zeros(0, np.int32))
-            out.append((int(r.request_id), int(r.status), tho, th, float(r.t_submit_us), float(r.t_done_us)))
+        for rid, status, nt, tho_at, th_at, t_submit, t_done in self._records[:n].tolist():
+            tho = _copy_i32(tho_at, nt + 1)
+            th = _copy_i32(th_at, int(tho[nt])) if tho[nt] > 0 else np.zeros(0, np.int32)
+            out.append((rid, status, tho, th, t_submit, t_done))
         return out
 
     def replay(self, pool, arrival_us, picks):

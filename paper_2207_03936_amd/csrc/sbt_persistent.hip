@@ -17,10 +17,11 @@ using namespace sbt;
 // its static LDS holds the event's Shared block.  For B = 64 a workgroup of
 // any number of waves runs one event per wave, each with its own region of
 // the dynamic LDS (the Shared block, then the layout of lds_bytes(CAP,
-// own_cap) bytes), and no wave ever waits for another.
+// own_cap) bytes), and no wave ever waits for another.  With direct, group i
+// runs event i and ends: neither counter nor order is read.
 template <int B, int CAP>
 __global__ __launch_bounds__(B == 64 ? 64 * kMaxEventsPerBlock : B) __attribute__((amdgpu_waves_per_eu(
-    B == 256 ? 5 : 4))) void k_persistent(sbt_params P, HitsArgs H, Work W0, int own_cap, int sortcap)
+    B == 256 ? 5 : 4))) void k_persistent(sbt_params P, HitsArgs H, Work W0, int own_cap, int sortcap, int direct)
 {
     uint32_t lo = 0;
     Shared<B> *sp;
@@ -41,13 +42,20 @@ __global__ __launch_bounds__(B == 64 ? 64 * kMaxEventsPerBlock : B) __attribute_
         W.base = opq_global(W0.base);
         W.H = opq(W0.H);
         W.E = opq(W0.E);
-        if (tid<B>() == 0) {
-            const int idx = (int)atomicAdd(ws_counterp(W), 1u);
-            S.e = idx < H.n_events ? ws_orderp(W)[idx] : -1;
+        int e;
+        if (direct) {
+            e = (int)blockIdx.x;
+            if (B == 64) e = e * (int)(blockDim.x >> 6) + uni((int)(threadIdx.x >> 6));
+            if (e >= H.n_events) break;
+        } else {
+            if (tid<B>() == 0) {
+                const int idx = (int)atomicAdd(ws_counterp(W), 1u);
+                S.e = idx < H.n_events ? ws_orderp(W)[idx] : -1;
+            }
+            ev_sync<B>();
+            e = uni(S.e);
+            if (e < 0) break;
         }
-        ev_sync<B>();
-        const int e = uni(S.e);
-        if (e < 0) break;
         int hb, N;
         const int st = load_event<B>(P, H, e, S, &hb, &N);
         if (tid<B>() == 0) ws_evinfo(W)[e].st = st;
@@ -67,6 +75,7 @@ __global__ __launch_bounds__(B == 64 ? 64 * kMaxEventsPerBlock : B) __attribute_
             ws_evinfo(W)[e].nt = 0;
             ws_evinfo(W)[e].nh = 0;
         }
+        if (direct) break;
         ev_sync<B>();
     }
 }

@@ -99,6 +99,23 @@ def test_windows_that_close_the_circle_of_small_modules(tuning, window):
         _check(ev, mz[0], tuning, phi_window_seeding=window, phi_window_forwarding=window, max_doublet_candidates=K)
 
 
+@pytest.mark.parametrize("n", [1, 2, 255, 256, 257, 1025, 4096, 4097])
+def test_batch_sizes_at_the_launch_rules(n):
+    """A workgroup per event at most one per CU (no order, no counter) and
+    above, and the joint scan and write up to 4,096 events and above."""
+    b = synth.make_batch("tiny", n)
+    print(f"[gpu] tiny x {n}", flush=True)
+    want = oracle.reconstruct(b)
+    dev, p = sbt.DeviceBatch(b), sbt.make_params(b.module_z)
+    for tuning in (None, (64, 4, 256, 4096, 4), (64, 1, 256, 4096, 3), (256, 2, 256), (1024, 1, 1536)):
+        ctx = sbt.Context(p, b.n_events, b.n_hits, sbt.make_tuning(*tuning) if tuning else None)
+        got = ctx.reconstruct(dev).to_host()
+        for g, w in zip(got[:3], want):
+            assert np.array_equal(g, w)
+        assert got[3].size == n and not got[3].any()
+        ctx.close()
+
+
 @pytest.mark.parametrize("seeding", [0.0, -1.0, 1e-40, 0.04, float("inf"), float("nan")])
 @pytest.mark.parametrize("forwarding", [0.0, 1e-40, 0.04, float("inf"), float("nan")])
 def test_scatter_bounds_at_the_edges_of_their_type(seeding, forwarding):

@@ -249,6 +249,7 @@ typedef struct sbt_context sbt_context;
  *     per compute unit and 256-hit LDS slots when there are more than two
  *     events per compute unit, else 512 lanes, two per compute unit,
  *     448-hit slots;
+ *   - one event of at most 4,500 hits: 512 lanes, 1,024-hit slots;
  *   - at most one event per compute unit, or at most two of 4,000 hits or
  *     more on average, or any number of 9,000 hits or more on average:
  *     1,024 lanes, one workgroup per compute unit, 1,536-hit slots;
@@ -258,8 +259,8 @@ typedef struct sbt_context sbt_context;
  *     slots (deferred_window_hits);
  *   - other events of 4,000 hits or more on average: 512 lanes, two per
  *     compute unit, 768-hit slots;
- *   - six or more other events per compute unit: 512 lanes, three per
- *     compute unit, 448-hit slots;
+ *   - eight and a half or more other events per compute unit: 512 lanes,
+ *     three per compute unit, 448-hit slots;
  *   - otherwise 512 lanes, two per compute unit, 672-hit slots.
  * sbt_context_set_tuning and sbt_autotune install one configuration for
  * every later call; sbt_context_get_tuning reports the installed one, or

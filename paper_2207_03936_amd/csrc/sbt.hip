@@ -1245,34 +1245,37 @@ sbt_tuning default_tuning()
 }
 
 // Launch configuration for a batch of E events and H hits on a device of
-// `cus` compute units.  A batch of at most one event per compute unit, or at
-// most two large ones (4,000 hits or more on average), runs 1,024 lanes per
-// event, one workgroup per CU with 1,536-hit slots: each event then finishes
-// sooner, and there are too few events to fill the device twice.  Larger
-// batches run 512 lanes, two workgroups per CU; batches of large events take
-// 768-hit slots (the largest that still fit two workgroups' LDS on a CU), so
-// that their busiest modules stay in LDS rather than in memory.  Batches of
-// six or more mid-size events per CU are throughput-bound rather than bound
-// by their largest event, and run 512 lanes, three workgroups per CU, with
-// 448-hit slots (the instance held to six waves per SIMD): 1.05x the
-// throughput of two per CU on 1,536 mu = 7.6 events, 1.16-1.19x on 2,000 to
-// 8,000 (1,280: 0.98x); the
-// few events with a larger module run from memory, which a long batch hides
-// but a batch of 1,000 does not (0.62 ms against 0.45).  Long batches of
-// large events (fifteen or more per CU) run the same way in two passes: the
-// events whose busiest module exceeds 448 hits (38 % of mu in U{1..25}) are
-// set aside and then run with 768-hit slots, two per CU (mu in U{1..25} x
-// 10,000: 5.59 ms against 6.03; x 4,000: 2.33 against 2.42; x 2,500: 1.58
-// against 1.54, so not below fifteen per CU).  Batches
-// of very large events (9,000 hits or more on average) have modules beyond
-// the 768-hit slots, and run 1,024 lanes per event with 1,536-hit slots
-// whatever their number (mu = 30 x 2,000: 3.72 ms against 4.48 ms).
-// Batches of small events (2,500 hits or fewer on average), whose modules
-// fit 256-hit slots, run 256 lanes, five workgroups per CU, when there are
-// more than two per CU (1,024 events of about 860 hits: 0.20 ms against
-// 0.34 ms with 512 lanes x 2 per CU; 2,048: 0.36 against 0.63), and 512
-// lanes, two per CU, with 448-hit slots when there are fewer (128 to 512
-// such events: 0.17-0.21 ms, about 10 % below 1,024 lanes per event).
+// `cus` compute units (times: us a call, best configuration and its rival).
+//  - At most one event per compute unit, or at most two large ones (4,000 hits
+//    or more on average): 1,024 lanes per event, one workgroup per CU with
+//    1,536-hit slots.  The batch takes as long as its largest event, and there
+//    are too few events to fill the device twice (mu in U{1..25} x 256: 212,
+//    254 with 512 lanes x 2 per CU; x 1,000: 588, 388).
+//  - One event of at most 4,500 hits: 512 lanes, 1,024-hit slots.  Its steps'
+//    work fits eight waves, and barriers and scans over eight cost less than
+//    over sixteen (2,614 hits: 104, 110; 3,500: 121, 126; 4,510: 136, 136; with
+//    two workgroups' 768-hit slots 6,046: 156, 145).
+//  - Larger batches: 512 lanes, two workgroups per CU with 672-hit slots;
+//    batches of large events with 768-hit slots (the largest of which two fit a
+//    CU), so that their busiest modules stay in LDS (mu in U{1..25} x 1,000:
+//    388, 706).
+//  - From 8.5 mid-size events per CU on: 512 lanes, three per CU with 448-hit
+//    slots (the instance held to six waves per SIMD).  The few events with a
+//    larger module run from memory at about three times the time, which a long
+//    batch hides (mu = 7.6 x 2,300: 590, 625; x 4,000: 840, 1,063) and a
+//    shorter one does not (x 2,000: 574, 534; x 1,000: 515, 279).
+//  - From fifteen large events per CU on: the same in two passes.  The events
+//    whose busiest module exceeds 448 hits (38 % of mu in U{1..25}) are set
+//    aside and then run with 768-hit slots, two per CU (x 10,000: 3,450, 3,640
+//    in one pass with 768-hit slots; x 4,000: 1,497, 1,486).
+//  - Very large events (9,000 hits or more on average) have modules beyond the
+//    768-hit slots: 1,024 lanes with 1,536-hit slots whatever their number
+//    (mu = 30 x 1,000: 1,040, 2,680).
+//  - Small events (2,500 hits or fewer on average), whose modules fit 256-hit
+//    slots: 256 lanes, five workgroups per CU, when there are more than two
+//    per CU (800 events of about 1,260 hits: 143, 205 with 512 lanes x 2;
+//    2,000: 240, 403), and 512 lanes with 448-hit slots when there are fewer
+//    (one of 500 hits: 71, 79 with 1,024 lanes).
 sbt_tuning size_tuning(int E, int H, int cus)
 {
     sbt_tuning t = default_tuning();
@@ -1287,6 +1290,9 @@ sbt_tuning size_tuning(int E, int H, int cus)
         } else {
             t.lds_window_hits = 448;
         }
+    } else if (E == 1 && H <= 4500) {
+        t.blocks_per_cu = 1;
+        t.lds_window_hits = 1024;
     } else if (E <= cus || (E <= 2 * cus && large) || huge) {
         t.threads_per_event = 1024;
         t.blocks_per_cu = 1;
@@ -1297,7 +1303,7 @@ sbt_tuning size_tuning(int E, int H, int cus)
         t.deferred_window_hits = 768;
     } else if (large) {
         t.lds_window_hits = 768;
-    } else if (E >= 6 * cus) {
+    } else if (2LL * E >= 17LL * cus) {
         t.blocks_per_cu = 3;
         t.lds_window_hits = 448;
     }

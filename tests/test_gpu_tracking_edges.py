@@ -116,6 +116,27 @@ def test_batch_sizes_at_the_launch_rules(n):
         ctx.close()
 
 
+@pytest.mark.parametrize("n,hits,want", [(1, 2500, (512, 2, 448)), (1, 2501, (512, 1, 1024)), (1, 4500, (512, 1, 1024)),
+                                         (1, 4501, (1024, 1, 1536)), (2, 5002, (1024, 1, 1536)), (-1, 3000, (512, 2, 672)),
+                                         (0, 3000, (512, 3, 448))])
+def test_configuration_at_the_lines_of_the_rule(n, hits, want):
+    """One event by its hits; n <= 0: 8.5 events per CU, and n fewer."""
+    import torch
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    rng = np.random.default_rng(hits)
+    mod = [250 if hits > 2000 else 100] * 10
+    mod[5] += (hits if n in (1,) else 3000) - sum(mod)
+    ev, mz = _event(rng, mod, 90)
+    p = sbt.make_params(mz)
+    E = n if n > 0 else (17 * cus + 1) // 2 + n
+    ctx = sbt.Context(p, E, hits if n > 0 else hits * E)
+    t = ctx.get_tuning()
+    assert (t.threads_per_event, t.blocks_per_cu, t.lds_window_hits, t.deferred_window_hits) == want + (0,)
+    ctx.close()
+    if n == 1:
+        _check([ev], mz)
+
+
 @pytest.mark.parametrize("seeding", [0.0, -1.0, 1e-40, 0.04, float("inf"), float("nan")])
 @pytest.mark.parametrize("forwarding", [0.0, 1e-40, 0.04, float("inf"), float("nan")])
 def test_scatter_bounds_at_the_edges_of_their_type(seeding, forwarding):

@@ -805,8 +805,8 @@ uint32_t tuning_lds(const sbt_tuning &T)
 // CU has LDS to spare behind its 1,536-hit slots (6 KB of flag bits are 49,152
 // hits more), so the flags of every event fit and dense events beyond
 // lds_owner_hits stay out of the memory form: mu = 30 x 400, of which one event in
-// ten has more than 16,384 hits, takes 0.60 ms instead of 1.05.  A smaller
-// lds_owner_hits is taken as it is.
+// ten has more than 16,384 hits, took 0.60 ms instead of 1.05 with this alone.
+// A smaller lds_owner_hits is taken as it is.
 sbt_tuning launch_tuning(const sbt_tuning &T)
 {
     sbt_tuning t = T;

@@ -8,18 +8,23 @@
 // Per-event state lives in the workspace, in regions indexed by the event's
 // absolute hit offset hb (capacity N = hits of the event):
 //   hs      16-byte sorted hits {x, y, z, phi16 | id << 16} by sorted position
-//   owner   one bit per hit id: set once a track has taken the hit (the
-//           method only ever asks whether a hit is flagged; which track
-//           holds it is settled by the claim keys)
-//   claim   u64 per hit id: minimum claim key of the current stage (the LDS
-//           instantiation keeps the claims on followers' best hits in LDS,
-//           by window position, and only the seed hits' claims here)
-//   link    two u16 per hit id: the previous hit of the owning track, and
-//           the record of the accepted track whose key is this id
-//   rec     32-byte forming-track records (one per seed; <= N) and a 16-byte
-//           auxiliary record each (search result, seed fit, filter outcome)
-//   lists   six u16 lists of the memory instantiation (active tracks x2,
-//           final tracks, unflagged positions x2, unflagged ranks)
+//   owner   one bit per hit: set once a track has taken the hit (the method
+//           only ever asks whether a hit is flagged; which track holds it is
+//           settled by the claim keys).  Memory form: by hit id
+//   claim   u64 per hit: minimum claim key of the current stage, for the
+//           memory form (by id) and for the stages that the LDS form settles
+//           exactly (by sorted position)
+//   link    two u16 per hit (LDS form: by sorted position; memory form: by id):
+//           the previous hit of the owning track, and the record of the
+//           accepted track whose key is this id
+//   rec     memory form: 32-byte forming-track records (one per seed; <= N)
+//           and a 16-byte auxiliary record each (search result, seed fit,
+//           filter outcome).  LDS form: 16-byte final records
+//   lists   memory form: six u16 lists (active tracks x2, final tracks,
+//           unflagged positions x2, unflagged ranks).  LDS form: the ids by
+//           sorted position
+// The LDS form keeps its forming tracks in registers, and the sorted hits,
+// flags and claims of the modules around a step in LDS.
 // Hit ids, keys and record indices are 16-bit (events hold <= 65,535 hits).
 // Per-event bases are uniform; per-lane offsets are 32-bit.
 #pragma once
@@ -1056,7 +1061,10 @@ __device__ __forceinline__ int pendulum_quad(const uint16_t *F, int nf, int j, i
 // Measured against the form before it (tracks as 32-byte records in memory,
 // hits named by id, four barriers a step; microseconds a call): one event of
 // 500 hits 121 -> 81, one mu = 7.6 event 181 -> 124, mu = 7.6 x 1,000 452 ->
-// 350, mu in U{1..25} x 10,000 5,796 -> 4,142.
+// 350, mu in U{1..25} x 10,000 5,796 -> 4,142.  With the shared lists of
+// unflagged positions, four lanes per middle hit, the bound as first best key
+// and walks over several hits at a time, and fewer launches around it, the
+// same calls take 71, 117, 284 and 3,435.
 
 struct LWin {
     const Hit16 *h;
@@ -1243,9 +1251,9 @@ struct Free {
 // otherwise.  A new seed's search into t+1 runs on the lanes that made it;
 // seed and result go to the seeds table.  (More lanes for a middle hit, two or
 // four to a doublet's walk, shorten the chain but are more instructions, which
-// the SIMDs have no room for where a CU holds two events: sixteen lanes take
-// 317 us for mu = 7.6 x 1,000, eight 294, these four 297, and 1,703, 1,618 and
-// 1,606 for mu in U{1..25} x 4,000.)
+// the SIMDs have no room for where a CU holds two events: with walks of one
+// hit at a time sixteen lanes took 317 us for mu = 7.6 x 1,000, eight 294,
+// these four 297, and 1,703, 1,618 and 1,606 for mu in U{1..25} x 4,000.)
 template <int B, int CAP, int KQ, bool kCand>
 __device__ __forceinline__ void seed_pass(const Prm &P, uint32_t lo, const uint32_t *cand, const Step &st,
                                           Shared<B> &S, const Free &fr, bool more, bool gc)

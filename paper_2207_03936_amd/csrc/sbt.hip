@@ -829,20 +829,39 @@ const void *persistent_kernel(int tpe, int cap)
     }
 }
 
+// The slot capacity a tuning is launched with.  Three or more 512-lane
+// workgroups per CU with 448-hit slots get 480-hit slots where their flags
+// leave the LDS for it (a third of a CU's in 1,280-byte steps, 53,760 bytes,
+// less the static part): fewer events run from memory or in a second pass
+// (mu in U{1..25} x 4,000: 1,442 us instead of 1,501, x 10,000: 3,387 instead
+// of 3,394; mu = 7.6 x 4,000: 826 instead of 833).
+int launch_cap(const sbt_tuning &T)
+{
+    constexpr uint32_t third = 53760 - 1536;
+    const int cap = effective_cap(T.lds_window_hits);
+    const bool dense = T.threads_per_event == 512 && T.blocks_per_cu >= 3 && cap == 448;
+    return dense && lds_bytes(480, T.lds_owner_hits) <= third ? 480 : cap;
+}
+
+uint32_t launch_lds(const sbt_tuning &T)
+{
+    return T.threads_per_event == 64 ? tuning_lds(T) : lds_bytes(launch_cap(T), T.lds_owner_hits);
+}
+
 // The instance held to six waves per SIMD, which three or more 512-lane
 // workgroups per CU with 448-hit slots take (with the default register budget
 // only two fit a CU); nullptr for other tunings.
 const void *dense_fn(const sbt_tuning &T)
 {
     if (T.threads_per_event != 512 || T.blocks_per_cu < 3) return nullptr;
-    return persistent_kernel_512_dense(effective_cap(T.lds_window_hits));
+    return persistent_kernel_512_dense(launch_cap(T));
 }
 
 // the persistent kernel a tuning runs
 const void *persistent_fn(const sbt_tuning &T)
 {
     const void *fn = dense_fn(T);
-    return fn ? fn : persistent_kernel(T.threads_per_event, effective_cap(T.lds_window_hits));
+    return fn ? fn : persistent_kernel(T.threads_per_event, launch_cap(T));
 }
 
 int device_cus(int *cus)
@@ -866,7 +885,7 @@ int persistent_occupancy(const sbt_tuning &T, int *occ)
 {
     const void *fn = persistent_fn(T);
     if (!fn) return SBT_ERR_INVALID_ARG;
-    const size_t lds = tuning_lds(T);
+    const size_t lds = launch_lds(T);
     if (int rc = allow_lds(fn, lds)) return rc;
     HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(occ, fn, block_lanes(T), lds));
     return SBT_OK;
@@ -920,8 +939,8 @@ int launch_pass(const sbt_params &P, const sbt_tuning &T0, const HitsArgs &H, co
         pass == Pass::kOnly && !dense && grid <= cus && H.n_events <= grid * events_per_block(T);
     if (pass == Pass::kSecond) hipLaunchKernelGGL(k_defer, dim3(1), dim3(kDeferThreads), 0, s, H, W);
     else if (!direct) hipLaunchKernelGGL(k_prepare, dim3(1), dim3(kOrderThreads), 0, s, H, W);
-    const int cap = effective_cap(T.lds_window_hits);
-    const uint32_t lds = tuning_lds(T);
+    const int cap = launch_cap(T);
+    const uint32_t lds = launch_lds(T);
     int own_cap = T.lds_owner_hits;
     int sortcap = lds_sortcap(cap, T.lds_owner_hits);
     // the six-waves instance sets the events aside that do not fit the LDS form
@@ -1260,14 +1279,15 @@ sbt_tuning default_tuning()
 //    CU), so that their busiest modules stay in LDS (mu in U{1..25} x 1,000:
 //    388, 706).
 //  - From 8.5 mid-size events per CU on: 512 lanes, three per CU with 448-hit
-//    slots (the instance held to six waves per SIMD).  The few events with a
+//    slots (launched with 480; the instance held to six waves per SIMD).  The few events with a
 //    larger module run from memory at about three times the time, which a long
 //    batch hides (mu = 7.6 x 2,300: 590, 625; x 4,000: 840, 1,063) and a
 //    shorter one does not (x 2,000: 574, 534; x 1,000: 515, 279).
 //  - From fifteen large events per CU on: the same in two passes.  The events
-//    whose busiest module exceeds 448 hits (38 % of mu in U{1..25}) are set
-//    aside and then run with 768-hit slots, two per CU (x 10,000: 3,450, 3,640
-//    in one pass with 768-hit slots; x 4,000: 1,497, 1,486).
+//    whose busiest module exceeds the slots (38 % of mu in U{1..25} exceed 448
+//    hits) are set aside and then run with 768-hit slots, two per CU
+//    (x 10,000: 3,387, 3,575 in one pass with 768-hit slots; x 4,000: 1,442,
+//    1,484).
 //  - Very large events (9,000 hits or more on average) have modules beyond the
 //    768-hit slots: 1,024 lanes with 1,536-hit slots whatever their number
 //    (mu = 30 x 1,000: 1,040, 2,680).

@@ -82,8 +82,8 @@ __global__ __launch_bounds__(B == 64 ? 64 * kMaxEventsPerBlock : B) __attribute_
 
 #if SBT_TPE == 512
 // The 512-lane kernel held to six waves per SIMD (at most 80 VGPRs), so that
-// three workgroups with 448-hit slots (49.5 KB of LDS each) share a compute
-// unit: more events in flight for long batches.  With defer, events whose
+// three workgroups with 448- or 480-hit slots (49.5 or 52.7 KB of LDS each)
+// share a compute unit: more events in flight for long batches.  With defer, events whose
 // busiest module or flag count does not fit the LDS form are not run from
 // memory but listed for a second pass.  The body is otherwise k_persistent's
 // for B = 512, written out again: routing both kernels through one inlined
@@ -163,7 +163,11 @@ const void *SBT_CAT(persistent_kernel_, SBT_TPE)(int cap)
 #if SBT_TPE == 512
 const void *persistent_kernel_512_dense(int cap)
 {
-    return cap == 448 ? reinterpret_cast<const void *>(k_persistent_dense<448>) : nullptr;
+    switch (cap) {
+    case 448: return reinterpret_cast<const void *>(k_persistent_dense<448>);
+    case 480: return reinterpret_cast<const void *>(k_persistent_dense<480>);
+    default: return nullptr;
+    }
 }
 #endif
 

@@ -137,6 +137,16 @@ def test_configuration_at_the_lines_of_the_rule(n, hits, want):
         _check([ev], mz)
 
 
+@pytest.mark.parametrize("flags", [4096, 16384, 25000, 40000])
+@pytest.mark.parametrize("deferred", [0, 768])
+def test_slots_of_the_six_waves_instance(deferred, flags):
+    """Modules around its 448 and 480 hits, with flags that leave LDS for the
+    larger slots and that do not, in one pass and in two."""
+    rng = np.random.default_rng(deferred + flags)
+    ev, mz = zip(*[_event(rng, [n] * 6, 150) for n in (447, 448, 449, 479, 480, 481, 600)])
+    _check(ev, mz[0], (512, 3, 448, flags, 1, deferred))
+
+
 @pytest.mark.parametrize("seeding", [0.0, -1.0, 1e-40, 0.04, float("inf"), float("nan")])
 @pytest.mark.parametrize("forwarding", [0.0, 1e-40, 0.04, float("inf"), float("nan")])
 def test_scatter_bounds_at_the_edges_of_their_type(seeding, forwarding):

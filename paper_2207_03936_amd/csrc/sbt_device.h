@@ -987,57 +987,36 @@ __device__ __forceinline__ int pendulum_pick(const uint16_t *F, int nf, int j, i
     return pos;
 }
 
-// The same picks for K = 4 with the four partner ranks of a middle hit on
-// the four lanes of a quad (c = lane & 3): lane c loads the c-th unflagged
-// position upwards from s0 and the c-th downwards below it and turns them
-// into visit ranks; the quad exchanges the eight ranks, every lane merges
-// the two ascending lists and keeps the c-th smallest, whose rank gives its
-// position back (rank 2o: s0 + o, rank 2o - 1: s0 - o).  All four lanes of
-// the quad must be active.
-template <int CTRL>
-__device__ __forceinline__ int quad_bcast(int v)
-{
-    return __builtin_amdgcn_mov_dpp(v, CTRL, 0xf, 0xf, false);
-}
-
+// One of the K = 4 picks for lane c = 0..3 of a middle hit, a different one
+// for each lane, or -1: which lane gets which does not matter, as the lanes'
+// doublets meet in a minimum.  The unflagged positions upwards from s0 and
+// those downwards below it are two lists of ascending visit ranks (2o and 2o -
+// 1 for an offset o); the four smallest of two ascending lists of four are
+// min(up[c], down[3 - c]), so a lane loads those two and needs no other lane.
+// (Exchanging the eight ranks and merging them to the c-th smallest took some
+// 60 instructions more on the step's chain: mu = 7.6 x 1,000 279 us, now 274;
+// mu in U{1..25} x 1,000 392, now 383; one event of 500 hits 71.6, now 70.0.)
 __device__ __forceinline__ int pendulum_quad(const uint16_t *F, int nf, int j, int s0, int na, int hu, int hd, int c)
 {
     constexpr int kInf = 0x7fffffff;
-    int ru = kInf, rd = kInf;
+    int ru = kInf, rd = kInf, pu = 0, pd = 0;
     if (c < nf) {
         int iu = j + c;
         if (iu >= nf) iu -= nf;
-        int id = j - 1 - c;
-        if (id < 0) id += nf;
-        const int pu = at(F, iu), pd = at(F, id);
+        pu = at(F, iu);
         int o = pu - s0;
         if (o < 0) o += na;
         if (o <= hu) ru = 2 * o;
-        int od = s0 - pd;
-        if (od < 0) od += na;
-        if (od >= 1 && od <= hd) rd = 2 * od - 1;
     }
-    int u0 = quad_bcast<0x00>(ru), u1 = quad_bcast<0x55>(ru), u2 = quad_bcast<0xAA>(ru), u3 = quad_bcast<0xFF>(ru);
-    int d0 = quad_bcast<0x00>(rd), d1 = quad_bcast<0x55>(rd), d2 = quad_bcast<0xAA>(rd), d3 = quad_bcast<0xFF>(rd);
-    int pick = kInf;
-#pragma unroll
-    for (int step = 0; step < 4; ++step) {
-        const bool up = u0 < d0;
-        const int take = up ? u0 : d0;
-        if (step == c) pick = take;
-        if (up) { u0 = u1; u1 = u2; u2 = u3; u3 = kInf; }
-        else { d0 = d1; d1 = d2; d2 = d3; d3 = kInf; }
+    if (3 - c < nf) {
+        int id = j - 4 + c;
+        if (id < 0) id += nf;
+        pd = at(F, id);
+        int o = s0 - pd;
+        if (o < 0) o += na;
+        if (o >= 1 && o <= hd) rd = 2 * o - 1;
     }
-    if (pick == kInf) return -1;
-    int pos;
-    if ((pick & 1) == 0) {
-        pos = s0 + (pick >> 1);
-        if (pos >= na) pos -= na;
-    } else {
-        pos = s0 - ((pick + 1) >> 1);
-        if (pos < 0) pos += na;
-    }
-    return pos;
+    return min(ru, rd) == kInf ? -1 : ru < rd ? pu : pd;
 }
 
 

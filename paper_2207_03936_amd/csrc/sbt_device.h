@@ -1042,8 +1042,8 @@ __device__ __forceinline__ int pendulum_quad(const uint16_t *F, int nf, int j, i
 // 500 hits 121 -> 81, one mu = 7.6 event 181 -> 124, mu = 7.6 x 1,000 452 ->
 // 350, mu in U{1..25} x 10,000 5,796 -> 4,142.  With the shared lists of
 // unflagged positions, four lanes per middle hit, the bound as first best key
-// and walks over several hits at a time, and fewer launches around it, the
-// same calls take 71, 117, 284 and 3,435.
+// and walks over several hits at a time, partners without an exchange, and
+// fewer launches around it, the same calls take 71, 117, 277 and 3,220.
 
 struct LWin {
     const Hit16 *h;

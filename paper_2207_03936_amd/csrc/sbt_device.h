@@ -570,8 +570,8 @@ struct Shared {
     int status;
     int e;
     int maxmod;          // hits of the event's largest module
+    alignas(16) int ctl[4];   // LDS form: seeds of a step by its parity (0, 1), a tie of claims, final records (read as one int4)
     int scan[2 * (B / 64)];
-    int ctl[4];          // LDS form: seeds of a step by its parity (0, 1), a tie of claims, final records
     int nfree[2][2][B / 64];   // free track slots of each wave, by step parity: sets 0 | 1 << 16, sets 2 | 3 << 16
     union alignas(16) {
         uint8_t mtab[(SBT_MAX_EVENT_HITS + 64) / 64];   // module of every 64th hit (sort)

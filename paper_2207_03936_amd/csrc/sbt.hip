@@ -145,19 +145,19 @@ __global__ __launch_bounds__(B) void k_compact(HitsArgs H, Work W, int lds_bytes
 
 // batched form ----------------------------------------------------------------
 
-// Resets the work counter and orders the events by size, largest first, so
-// the persistent workgroups start the longest events early (the order of
+// Sets the work counter to start and orders the events by size, largest first,
+// so the persistent workgroups start the longest events early (the order of
 // processing never changes an event's result).  Counting sort on N / 64.
 constexpr int kOrderThreads = 256;    // small, so it fits beside another stream's persistent workgroups
 constexpr int kOrderClasses = 1024;
 constexpr int kOrderBatch = 4;        // events whose offsets a lane loads together
-__global__ __launch_bounds__(kOrderThreads) void k_prepare(HitsArgs H, Work W)
+__global__ __launch_bounds__(kOrderThreads) void k_prepare(HitsArgs H, Work W, unsigned int start)
 {
     __shared__ int hist[kOrderClasses + 1];
     __shared__ int fill[kOrderClasses];
     __shared__ int sw[2 * (kOrderThreads / 64)];
     if (threadIdx.x == 0) {
-        *ws_counterp(W) = 0u;
+        *ws_counterp(W) = start;
         *ws_defer_countp(W) = 0u;
     }
     for (int i = threadIdx.x; i <= kOrderClasses; i += kOrderThreads) hist[i] = 0;
@@ -928,6 +928,13 @@ enum class Pass { kOnly, kFirst, kSecond };
 // order matters: it sets the largest events beside smaller ones): one event of
 // 500 hits takes 71 us instead of 74, one mu = 7.6 event 125 instead of 129, 64
 // of them 142 instead of 146.
+// With more groups, each takes its first event by its own number.  The groups
+// of one XCD may start before another's, and where they raced for the first
+// events, several of the largest met on one compute unit: mu = 7.6 x 1,000 on
+// 256 lanes with 256-hit slots (every fourth event runs from memory) took 751
+// to 812 us, and takes 706; on 128 lanes 1,351 to 1,370, and 1,054; on the
+// rule's 512 lanes 274, and 269.  The
+// six-waves instance and second passes take all events from the counter.
 int launch_pass(const sbt_params &P, const sbt_tuning &T0, const HitsArgs &H, const Work &W, hipStream_t s, Pass pass)
 {
     const sbt_tuning T = launch_tuning(T0);
@@ -935,17 +942,22 @@ int launch_pass(const sbt_params &P, const sbt_tuning &T0, const HitsArgs &H, co
     int rc = persistent_grid(T, H.n_events, &grid);
     if (rc || (rc = device_cus(&cus))) return rc;
     const bool dense = dense_fn(T) != nullptr;
-    const bool direct =
-        pass == Pass::kOnly && !dense && grid <= cus && H.n_events <= grid * events_per_block(T);
-    if (pass == Pass::kSecond) hipLaunchKernelGGL(k_defer, dim3(1), dim3(kDeferThreads), 0, s, H, W);
-    else if (!direct) hipLaunchKernelGGL(k_prepare, dim3(1), dim3(kOrderThreads), 0, s, H, W);
+    const int groups = grid * events_per_block(T);
+    int take = kTakeQueue;
+    if (pass == Pass::kOnly && !dense) take = grid <= cus && H.n_events <= groups ? kTakeOwn : kTakeOwnThenQueue;
+    if (pass == Pass::kSecond) {
+        hipLaunchKernelGGL(k_defer, dim3(1), dim3(kDeferThreads), 0, s, H, W);
+    } else if (take != kTakeOwn) {
+        hipLaunchKernelGGL(k_prepare, dim3(1), dim3(kOrderThreads), 0, s, H, W,
+                           take == kTakeOwnThenQueue ? (unsigned int)std::min(groups, H.n_events) : 0u);
+    }
     const int cap = launch_cap(T);
     const uint32_t lds = launch_lds(T);
     int own_cap = T.lds_owner_hits;
     int sortcap = lds_sortcap(cap, T.lds_owner_hits);
     // the six-waves instance sets the events aside that do not fit the LDS form
-    // (defer), the others have the direct mode
-    int mode = dense ? pass == Pass::kFirst : direct;
+    // (defer) in a first pass
+    int mode = dense ? pass == Pass::kFirst : take;
     sbt_params Pc = P;
     HitsArgs Hc = H;
     Work Wc = W;

@@ -13,15 +13,36 @@
 
 using namespace sbt;
 
+// The next event of a group, or -1 (on one lane; see kTakeOwnThenQueue).  Own
+// events are taken by exchanging their entry of the order for -1, the others
+// are met once.
+template <int B>
+__device__ __forceinline__ int take_event(const Work &W, int E, int group, int take)
+{
+    int32_t *order = ws_orderp(W);
+    if (take == kTakeQueue) {
+        const int idx = (int)atomicAdd(ws_counterp(W), 1u);
+        return idx < E ? order[idx] : -1;
+    }
+    const int own = min((int)(gridDim.x * (B == 64 ? blockDim.x >> 6 : 1u)), E);
+    int e = group >= 0 && group < E ? atomicExch(&order[group], -1) : -1;
+    while (e < 0) {
+        const int idx = (int)atomicAdd(ws_counterp(W), 1u);
+        if (idx >= E + own) break;
+        e = idx < E ? order[idx] : atomicExch(&order[idx - E], -1);
+    }
+    return e;
+}
+
 // One event per group of B lanes.  For B > 64 the group is the workgroup and
 // its static LDS holds the event's Shared block.  For B = 64 a workgroup of
 // any number of waves runs one event per wave, each with its own region of
 // the dynamic LDS (the Shared block, then the layout of lds_bytes(CAP,
-// own_cap) bytes), and no wave ever waits for another.  With direct, group i
-// runs event i and ends: neither counter nor order is read.
+// own_cap) bytes), and no wave ever waits for another.  take: kTakeQueue,
+// kTakeOwn or kTakeOwnThenQueue.
 template <int B, int CAP>
 __global__ __launch_bounds__(B == 64 ? 64 * kMaxEventsPerBlock : B) __attribute__((amdgpu_waves_per_eu(
-    B == 256 ? 5 : 4))) void k_persistent(sbt_params P, HitsArgs H, Work W0, int own_cap, int sortcap, int direct)
+    B == 256 ? 5 : 4))) void k_persistent(sbt_params P, HitsArgs H, Work W0, int own_cap, int sortcap, int take)
 {
     uint32_t lo = 0;
     Shared<B> *sp;
@@ -35,6 +56,8 @@ __global__ __launch_bounds__(B == 64 ? 64 * kMaxEventsPerBlock : B) __attribute_
         sp = &S_wg;
     }
     Shared<B> &S = *sp;
+    int group = (int)blockIdx.x;   // -1: its own event is behind it
+    if (B == 64) group = group * (int)(blockDim.x >> 6) + uni((int)(threadIdx.x >> 6));
     for (;;) {
         // the workspace base is hidden from the optimiser per event, so the
         // pointers derived from it are not hoisted out of this loop
@@ -42,17 +65,13 @@ __global__ __launch_bounds__(B == 64 ? 64 * kMaxEventsPerBlock : B) __attribute_
         W.base = opq_global(W0.base);
         W.H = opq(W0.H);
         W.E = opq(W0.E);
-        int e;
-        if (direct) {
-            e = (int)blockIdx.x;
-            if (B == 64) e = e * (int)(blockDim.x >> 6) + uni((int)(threadIdx.x >> 6));
+        int e = group;
+        if (take == kTakeOwn) {
             if (e >= H.n_events) break;
         } else {
-            if (tid<B>() == 0) {
-                const int idx = (int)atomicAdd(ws_counterp(W), 1u);
-                S.e = idx < H.n_events ? ws_orderp(W)[idx] : -1;
-            }
+            if (tid<B>() == 0) S.e = take_event<B>(W, H.n_events, group, take);
             ev_sync<B>();
+            group = -1;
             e = uni(S.e);
             if (e < 0) break;
         }
@@ -75,7 +94,7 @@ __global__ __launch_bounds__(B == 64 ? 64 * kMaxEventsPerBlock : B) __attribute_
             ws_evinfo(W)[e].nt = 0;
             ws_evinfo(W)[e].nh = 0;
         }
-        if (direct) break;
+        if (take == kTakeOwn) break;
         ev_sync<B>();
     }
 }

@@ -226,3 +226,42 @@ def test_consolidation_at_the_lds_capacities(sizes):
     assert len(tho) > 1
     for a, w in zip(got, want):
         assert a.dtype == w.dtype and np.array_equal(a.view(np.uint32), np.ascontiguousarray(w).view(np.uint32))
+
+
+@pytest.mark.parametrize("tuning", [(64, 2, 256, 4096, 3), (128, 3, 256), (256, 2, 256), (512, 2, 672)])
+def test_own_events_then_the_queue(tuning):
+    """Batches around the number of event groups (each group's first event is
+    its own, the rest come from the counter), alone and while a batch of
+    another context holds the compute units, so that groups become resident
+    late and others take their events."""
+    import torch
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    groups = cus * tuning[1] * (tuning[4] if len(tuning) > 4 else 1)
+    pool = synth.make_batch("tiny", 64)
+    evs = [pool.event(i % 64) for i in range(2 * groups + 5)]
+    evs = [dict(x=e.x, y=e.y, z=e.z, module_counts=np.diff(e.module_offsets), truth=np.full(e.x.size, -1, np.int32))
+           for e in evs]
+    want = [oracle.reconstruct(pool.event(i)) for i in range(64)]
+    side = synth.make_batch("mu7.6", 600)
+    sdev, sp = sbt.DeviceBatch(side), sbt.make_params(side.module_z)
+    sctx, sout = sbt.Context(sp, side.n_events, side.n_hits), sbt.DeviceTracks(side.n_events, side.n_hits)
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    for n in (cus + 1, groups - 1, groups, groups + 1, 2 * groups + 5):
+        b = synth.concat(evs[:n], pool.module_z)
+        print(f"[gpu] {n} events on {groups} groups, {tuning}", flush=True)
+        dev, p = sbt.DeviceBatch(b), sbt.make_params(b.module_z)
+        ctx = sbt.Context(p, b.n_events, b.n_hits, sbt.make_tuning(*tuning))
+        out = sbt.DeviceTracks(b.n_events, b.n_hits)
+        for beside in (False, True, True):
+            torch.cuda.synchronize()
+            if beside:
+                sctx.reconstruct(sdev, sout, streams[0])
+            ctx.reconstruct(dev, out, streams[1])
+            torch.cuda.synchronize()
+            eto, tho, th, st = out.to_host()
+            assert not st.any()
+            assert np.array_equal(np.diff(eto), [want[i % 64][0][-1] for i in range(n)])
+            assert np.array_equal(th, np.concatenate([want[i % 64][2] for i in range(n)]))
+            assert np.array_equal(np.diff(tho), np.concatenate([np.diff(want[i % 64][1]) for i in range(n)]))
+        ctx.close()
+    sctx.close()

@@ -679,9 +679,6 @@ size_t carve(int32_t E, int32_t H, char *base, Work *W)
 
 bool is_pow_tpe(int v) { return v == 64 || v == 128 || v == 256 || v == 512 || v == 1024; }
 
-// dynamic LDS a workgroup may ask for (gfx950: 160 KiB per compute unit)
-constexpr size_t kMaxDynLds = 160 * 1024 - 1024;
-
 int check_hits(const sbt_hits *h)
 {
     if (!h) return SBT_ERR_INVALID_ARG;

@@ -508,9 +508,9 @@ __host__ __device__ constexpr uint32_t lay_own(int cap) { return lay_tab(cap) + 
 constexpr int kSortBins = 2048;
 __host__ __device__ constexpr uint32_t lds_sort_head() { return a16((kSortBins + 1u) * 4u); }
 
-__host__ __device__ inline uint32_t lds_bytes(int cap, int own_cap)
+__host__ __device__ constexpr uint32_t lds_bytes(int cap, int own_cap)
 {
-    const uint32_t sort = lds_sort_head() + 4u * 1024u;   // keys of 1,024 hits at least
+    constexpr uint32_t sort = lds_sort_head() + 4u * 1024u;   // keys of 1,024 hits at least
     const uint32_t track = cap > 0 ? lay_own(cap) + a16(4u * (uint32_t)((own_cap + 31) / 32) + 8u) : 0u;
     return sort > track ? sort : track;
 }
@@ -555,11 +555,16 @@ struct Lay {
 };
 
 // Forming tracks of the LDS form are held in registers, one per lane and
-// set; as many sets as the slots have hits per lane, at most four.
+// set; as many sets as the slots have hits per lane, so that an event whose
+// modules fit runs out of lanes only with more tracks at a step than a module
+// may have hits.  (At most four sets, which 64 lanes with 672-hit slots and
+// more and 128 with 768 exceed, sent events of more tracks through memory a
+// second time: mu = 7.6 x 500 on 64 lanes x 672 slots 1,587 us, now 672; mu in
+// U{1..25} x 300 on 128 x 768 1,560, now 642.)
 template <int B, int CAP>
 __host__ __device__ constexpr int track_sets()
 {
-    return CAP <= B ? 1 : (CAP + B - 1) / B > 4 ? 4 : (CAP + B - 1) / B;
+    return CAP <= B ? 1 : (CAP + B - 1) / B;
 }
 
 // static LDS shared by the stages of one event
@@ -572,10 +577,11 @@ struct Shared {
     int maxmod;          // hits of the event's largest module
     alignas(16) int ctl[4];   // LDS form: seeds of a step by its parity (0, 1), a tie of claims, final records (read as one int4)
     int scan[2 * (B / 64)];
-    int nfree[2][2][B / 64];   // free track slots of each wave, by step parity: sets 0 | 1 << 16, sets 2 | 3 << 16
     union alignas(16) {
         uint8_t mtab[(SBT_MAX_EVENT_HITS + 64) / 64];   // module of every 64th hit (sort)
-        int4 mt[SBT_MAX_MODULES];   // by traversal index: first sorted position, hits, nominal z (LDS form)
+        // LDS form: by traversal index the first sorted position, hits and
+        // nominal z; in w, by free_at, the free track slots of the waves
+        int4 mt[SBT_MAX_MODULES];
     };
 };
 
@@ -588,9 +594,50 @@ __host__ __device__ constexpr uint32_t shared_block_bytes()
     return a16((uint32_t)sizeof(Shared<B>));
 }
 template <int B>
-__host__ __device__ inline uint32_t event_region_bytes(int cap, int own_cap)
+__host__ __device__ constexpr uint32_t event_region_bytes(int cap, int own_cap)
 {
     return shared_block_bytes<B>() + lds_bytes(cap, own_cap);
+}
+
+// LDS of a compute unit, and the most dynamic LDS a workgroup may ask for
+constexpr uint32_t kCuLds = 160 * 1024, kMaxDynLds = kCuLds - 1024;
+
+// Lanes of the widest workgroup that runs events of B lanes: 64-lane events
+// as many to a workgroup as have room in its LDS.
+template <int B, int CAP>
+constexpr int max_block_lanes()
+{
+    if (B > 64) return B;
+    const int fit = (int)(kMaxDynLds / event_region_bytes<B>(CAP, 0));
+    return 64 * (fit < kMaxEventsPerBlock ? fit : kMaxEventsPerBlock);
+}
+
+// Waves per SIMD that a persistent kernel leaves registers for: four, five
+// with 256 lanes (five workgroups with 256-hit slots on a CU), and no more than
+// the LDS lets run, so that the sets of forming tracks stay in registers (with
+// four and five for all of them, 64 to 256 lanes spilled 8 to 133).
+template <int B, int CAP>
+constexpr int simd_waves()
+{
+    constexpr int most = B == 256 ? 5 : 4;
+    const int groups = (int)(kCuLds / event_region_bytes<B>(CAP, 0));
+    const int waves = (groups * (B / 64) + 3) / 4;
+    return waves < most ? waves : most;
+}
+
+// Where the free track slots of a wave stand in Shared::mt, for the sets
+// 2 h (low half) and 2 h + 1 (high half), by the parity of the step.
+template <int B, int CAP>
+constexpr int free_words()
+{
+    constexpr int words = (track_sets<B, CAP>() + 1) / 2;
+    static_assert(2 * words * (B / 64) <= SBT_MAX_MODULES, "free slots beside the module table");
+    return words;
+}
+template <int B, int CAP>
+__device__ __forceinline__ int &free_at(Shared<B> &S, int parity, int h, int wave)
+{
+    return S.mt[(parity * free_words<B, CAP>() + h) * (B / 64) + wave].w;
 }
 
 // per-event views of the workspace: pointers are derived on use from the
@@ -1506,14 +1553,12 @@ __device__ __forceinline__ bool track_lds(const Ev &v0, Shared<B> &S, bool write
     for (int i = tid<B>(); i < N; i += B) at(reinterpret_cast<uint32_t *>(link), (uint32_t)i) = 0xFFFFFFFFu;
     if (writeback)
         for (int i = tid<B>(); i < N; i += B) at(claim, (uint32_t)i) = kNoClaim;
-    if (tid<B>() < NW) {
-        S.nfree[0][0][tid<B>()] = SETS >= 2 ? 64 | (64 << 16) : 64;
-        S.nfree[0][1][tid<B>()] = SETS >= 4 ? 64 | (64 << 16) : SETS == 3 ? 64 : 0;
-    }
     if (tid<B>() < 4) S.ctl[tid<B>()] = 0;
-    if (tid<B>() < M) {
-        const int k = kmod(PP, (int)tid<B>());
-        S.mt[tid<B>()] = make_int4(S.mo[k], S.mo[k + 1] - S.mo[k], __float_as_int(PP.module_z[k]), 0);
+    if (tid<B>() < SBT_MAX_MODULES) {
+        // the first step finds every slot free
+        const int u = (int)tid<B>(), k = u < M ? kmod(PP, u) : 0, h = u / NW;
+        const int w = h >= free_words<B, CAP>() ? 0 : 2 * h + 1 < SETS ? 64 | (64 << 16) : 64;
+        S.mt[u] = make_int4(S.mo[k], S.mo[k + 1] - S.mo[k], __float_as_int(PP.module_z[k]), w);
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u)
@@ -1646,7 +1691,7 @@ __device__ __forceinline__ bool track_lds(const Ev &v0, Shared<B> &S, bool write
         const int4 nxt = S.mt[st.t + 2 < M ? st.t + 2 : 0];
         int fsl[(SETS + 1) / 2];
 #pragma unroll
-        for (int h = 0; h < (SETS + 1) / 2; ++h) fsl[h] = lane < NW ? S.nfree[(st.t + 1) & 1][h][lane] : 0;
+        for (int h = 0; h < (SETS + 1) / 2; ++h) fsl[h] = lane < NW ? free_at<B, CAP>(S, (st.t + 1) & 1, h, lane) : 0;
 #pragma unroll
         for (int i = 0; i < 6; ++i) {
             st.g[i] = st.g[i + 1];
@@ -1754,7 +1799,7 @@ __device__ __forceinline__ bool track_lds(const Ev &v0, Shared<B> &S, bool write
         }
         if (lane == 0) {
 #pragma unroll
-            for (int h = 0; h < (SETS + 1) / 2; ++h) S.nfree[t & 1][h][wv] = nf[2 * h] | (nf[2 * h + 1] << 16);
+            for (int h = 0; h < (SETS + 1) / 2; ++h) free_at<B, CAP>(S, t & 1, h, wv) = nf[2 * h] | (nf[2 * h + 1] << 16);
             if (wv == 0) S.ctl[t & 1] = 0;
         }
         ev_lds_sync<B>();

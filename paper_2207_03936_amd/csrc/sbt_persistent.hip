@@ -41,8 +41,8 @@ __device__ __forceinline__ int take_event(const Work &W, int E, int group, int t
 // own_cap) bytes), and no wave ever waits for another.  take: kTakeQueue,
 // kTakeOwn or kTakeOwnThenQueue.
 template <int B, int CAP>
-__global__ __launch_bounds__(B == 64 ? 64 * kMaxEventsPerBlock : B) __attribute__((amdgpu_waves_per_eu(
-    B == 256 ? 5 : 4))) void k_persistent(sbt_params P, HitsArgs H, Work W0, int own_cap, int sortcap, int take)
+__global__ __launch_bounds__((max_block_lanes<B, CAP>())) __attribute__((amdgpu_waves_per_eu(
+    simd_waves<B, CAP>()))) void k_persistent(sbt_params P, HitsArgs H, Work W0, int own_cap, int sortcap, int take)
 {
     uint32_t lo = 0;
     Shared<B> *sp;
@@ -56,25 +56,22 @@ __global__ __launch_bounds__(B == 64 ? 64 * kMaxEventsPerBlock : B) __attribute_
         sp = &S_wg;
     }
     Shared<B> &S = *sp;
-    int group = (int)blockIdx.x;   // -1: its own event is behind it
-    if (B == 64) group = group * (int)(blockDim.x >> 6) + uni((int)(threadIdx.x >> 6));
-    for (;;) {
+    int e = (int)blockIdx.x;
+    if (B == 64) e = e * (int)(blockDim.x >> 6) + uni((int)(threadIdx.x >> 6));
+    if (take == kTakeOwn) {
+        e = e < H.n_events ? e : -1;
+    } else {
+        if (tid<B>() == 0) S.e = take_event<B>(W0, H.n_events, e, take);
+        ev_sync<B>();
+        e = uni(S.e);
+    }
+    while (e >= 0) {
         // the workspace base is hidden from the optimiser per event, so the
         // pointers derived from it are not hoisted out of this loop
         Work W = W0;
         W.base = opq_global(W0.base);
         W.H = opq(W0.H);
         W.E = opq(W0.E);
-        int e = group;
-        if (take == kTakeOwn) {
-            if (e >= H.n_events) break;
-        } else {
-            if (tid<B>() == 0) S.e = take_event<B>(W, H.n_events, group, take);
-            ev_sync<B>();
-            group = -1;
-            e = uni(S.e);
-            if (e < 0) break;
-        }
         int hb, N;
         const int st = load_event<B>(P, H, e, S, &hb, &N);
         if (tid<B>() == 0) ws_evinfo(W)[e].st = st;
@@ -96,6 +93,9 @@ __global__ __launch_bounds__(B == 64 ? 64 * kMaxEventsPerBlock : B) __attribute_
         }
         if (take == kTakeOwn) break;
         ev_sync<B>();
+        if (tid<B>() == 0) S.e = take_event<B>(W, H.n_events, -1, take);
+        ev_sync<B>();
+        e = uni(S.e);
     }
 }
 

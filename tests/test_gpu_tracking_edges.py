@@ -265,3 +265,40 @@ def test_own_events_then_the_queue(tuning):
             assert np.array_equal(np.diff(tho), np.concatenate([np.diff(want[i % 64][1]) for i in range(n)]))
         ctx.close()
     sctx.close()
+
+
+def _peak_bound(b, e, eto, tho, th, misses):
+    """At least this many forming tracks meet at a step of event e where every
+    unflagged middle hit makes a seed: a seed lives through misses + 1 steps,
+    and a flagged hit is on a track of the result."""
+    M = b.n_modules
+    mo = b.module_offsets[e * M:e * M + M + 1] - b.event_offsets[e]
+    hits = th[tho[eto[e]]:tho[eto[e + 1]]]
+    taken = np.bincount(np.searchsorted(mo, hits, side="right") - 1, minlength=M)
+    free = (np.diff(mo) - taken)[::-1]              # by traversal index
+    seeds = [free[u] if u > 0 and u + 1 < M and free[u - 1] > 1 and free[u + 1] > 1 else 0 for u in range(M)]
+    return max(sum(seeds[u:u + misses + 1]) for u in range(M))
+
+
+@pytest.mark.parametrize("lanes,tuning,n", [
+    (256, (64, 1, 256, 16384), 250), (448, (64, 1, 448, 4096, 3), 440), (704, (64, 1, 672, 16384), 600),
+    (512, (128, 2, 448, 16384), 440), (768, (128, 1, 768, 16384), 700), (256, (256, 5, 256, 16384), 250),
+    (768, (256, 2, 672, 16384), 650), (1024, (512, 2, 672, 16384), 660), (512, (512, 3, 448, 16384), 470),
+    (512, (512, 3, 448, 16384, 1, 768), 470), (1024, (512, 2, 768, 16384), 760), (1024, (512, 1, 1024, 16384), 1000),
+    (2048, (1024, 1, 1536, 16384), 1500), (1024, None, 660)])
+def test_more_tracks_than_lanes(lanes, tuning, n):
+    """Events that give up the LDS form half way, with flags, links and claims
+    set, because more tracks meet at a step than the workgroup has lanes and
+    sets for, and are run again from memory; ordinary events beside them.
+    Noise modules under a window of the whole circle and no bound on the seeds'
+    scatter: every unflagged middle hit makes a seed."""
+    over = dict(phi_window_seeding=32767, max_scatter_seeding=float("inf"))
+    rng = np.random.default_rng(n + lanes)
+    ev, mz = zip(*[_event(rng, c, 30) for c in ([n] * 4 + [45] * 6, [40] * 10, [45] * 3 + [n] * 4 + [45] * 3)])
+    b = synth.concat(ev, mz[0])
+    want = oracle.reconstruct(b, **over)
+    for e in (0, 2):
+        assert np.diff(b.module_offsets[e * 10:e * 10 + 11]).max() <= (tuning[2] if tuning else 672) + 32
+        assert _peak_bound(b, e, *want, misses=1) > lanes
+    assert np.diff(want[0]).min() > 10      # tracks, and with them flags, before the noise
+    _check(ev, mz[0], tuning, form="batched" if tuning else "plain", **over)

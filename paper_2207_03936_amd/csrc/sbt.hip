@@ -35,9 +35,9 @@ using namespace sbt;
 constexpr int kPlainThreads = 512;
 constexpr int kPlainCap = 672;
 constexpr int kPlainOwnCap = 16384;
-// dynamic LDS of the plain compaction kernel: its LDS form (previous-hit
-// links and the key-ordered track list, 2 N + 2 (N / 3 + 1) bytes) fits
-// events of up to about 24,000 hits; larger ones take the memory form
+// dynamic LDS of the plain compaction kernel: holds links and tracks of events
+// of up to about 24,500 hits, and for those tracked in LDS the ids as well up to
+// about 14,000 (compact_form); larger ones take the memory form
 constexpr int kPlainCompactLds = 64 * 1024;
 
 template <int B>

@@ -2389,32 +2389,40 @@ __device__ __forceinline__ Acc accepted(const Ev &v, uint32_t r)
     return a;
 }
 
-// Whether the LDS form of the compaction fits: the previous-hit links (2 B
-// per hit), with kPos the ids by sorted position (2 B per hit), and the
-// record of each accepted track in key order (2 B per track; tracks are
-// disjoint with at least three hits, so at most N / 3).
-__host__ __device__ inline bool compact_fits_lds(int N, int lds_bytes, bool pos)
+// How the compaction of an event of N hits runs in lds_bytes of LDS: kWhole
+// holds the previous-hit links (2 B per hit), with pos the ids by sorted
+// position (2 B per hit), and the record of each accepted track in key order
+// (2 B per track; tracks are disjoint with at least three hits, so at most
+// N / 3); kIdsInMemory leaves the ids where they are, each read once beside
+// the walk of the links (200 events of 16,120 hits in the plain form: 371 us,
+// 685 with everything in memory; of 11,440 hits on 512 lanes with 480-hit
+// slots 259 and 401; of 6,500 on 256 lanes with 256-hit slots 216 and 367).
+enum class Compact { kMemory, kIdsInMemory, kWhole };
+__host__ __device__ constexpr Compact compact_form(int N, int lds_bytes, bool pos)
 {
-    return (int)a16(2u * (uint32_t)N) * (pos ? 2 : 1) + 2 * (N / 3 + 1) <= lds_bytes;
+    const int row = (int)a16(2u * (uint32_t)N), tracks = 2 * (N / 3 + 1);
+    if ((pos ? 2 : 1) * row + tracks <= lds_bytes) return Compact::kWhole;
+    return pos && row + tracks <= lds_bytes ? Compact::kIdsInMemory : Compact::kMemory;
 }
 
-// LDS form.  Pass 1 takes the keys in rounds of B (key = round * B + lane,
+// LDS form (kIds: the ids too).  Pass 1 takes the keys in rounds of B (key = round * B + lane,
 // loads coalesced, kCompactBatch rounds in flight), copies each previous-hit
 // link to LDS and ranks the keys that own a record with a ballot count over
 // the workgroup, which lists the records in key order.  Pass 2 gives each
 // listed track a lane: an exclusive scan of the lengths places its hits, and
 // the lane writes them, walking the links in LDS.
-template <int B, bool kPos>
+template <int B, bool kPos, bool kIds>
 __device__ __forceinline__ void compact_lds(const Ev &v, int *s_scan, int lds_bytes)
 {
     const int N = v.N;
     const uint32_t row = a16(2u * (uint32_t)N);
     uint16_t *lprev = reinterpret_cast<uint16_t *>(g_lds + v.lo);
-    uint16_t *lid = reinterpret_cast<uint16_t *>(g_lds + v.lo + row);   // kPos
-    uint16_t *lrec = reinterpret_cast<uint16_t *>(g_lds + v.lo + (kPos ? 2 : 1) * row);
-    const int rec_cap = (lds_bytes - (kPos ? 2 : 1) * (int)row) / 2;
+    uint16_t *lid = reinterpret_cast<uint16_t *>(g_lds + v.lo + row);   // kIds
+    uint16_t *lrec = reinterpret_cast<uint16_t *>(g_lds + v.lo + (kIds ? 2 : 1) * row);
+    const int rec_cap = (lds_bytes - (kIds ? 2 : 1) * (int)row) / 2;
     const uint32_t *link = reinterpret_cast<const uint32_t *>(v.link());   // prev | record << 16
     const int rounds = (N + B - 1) / B;
+    auto id = [&](uint32_t p) -> uint16_t { return kIds ? lid[p] : kPos ? at(v.sid(), p) : (uint16_t)p; };
     bool bad = false;
     int nt = 0;
     for (int j0 = 0; j0 < rounds; j0 += kCompactBatch) {
@@ -2424,7 +2432,7 @@ __device__ __forceinline__ void compact_lds(const Ev &v, int *s_scan, int lds_by
         for (int u = 0; u < kCompactBatch; ++u) {
             const int k = (j0 + u) * B + (int)tid<B>();
             w[u] = k < N ? at(link, (uint32_t)k) : ((uint32_t)kNone << 16);
-            if (kPos) d[u] = k < N ? at(v.sid(), (uint32_t)k) : (uint16_t)0;
+            if (kIds) d[u] = k < N ? at(v.sid(), (uint32_t)k) : (uint16_t)0;
         }
 #pragma unroll
         for (int u = 0; u < kCompactBatch; ++u) {
@@ -2433,7 +2441,7 @@ __device__ __forceinline__ void compact_lds(const Ev &v, int *s_scan, int lds_by
             const uint16_t r = (uint16_t)(w[u] >> 16);
             if (k < N) {
                 lprev[k] = (uint16_t)(w[u] & 0xFFFFu);
-                if (kPos) lid[k] = d[u];
+                if (kIds) lid[k] = d[u];
             }
             int tot;
             const int pos = nt + (block_count2<B>(r != kNone, false, s_scan, j0 + u, &tot) & 0xFFFF);
@@ -2467,12 +2475,12 @@ __device__ __forceinline__ void compact_lds(const Ev &v, int *s_scan, int lds_by
                 uint32_t p = R.last;
                 for (int j = len - 1; j >= 3; --j) {
                     if (p >= (uint32_t)N) { bad = true; break; }
-                    out[j] = kPos ? lid[p] : (uint16_t)p;
+                    out[j] = id(p);
                     p = lprev[p];
                 }
-                out[2] = kPos ? lid[R.h2] : (uint16_t)R.h2;
-                out[1] = kPos ? lid[R.h1] : (uint16_t)R.h1;
-                out[0] = kPos ? lid[R.h0] : (uint16_t)R.h0;
+                out[2] = id(R.h2);
+                out[1] = id(R.h1);
+                out[0] = id(R.h0);
             }
         }
     }
@@ -2534,12 +2542,18 @@ __device__ __forceinline__ void compact_mem(const Ev &v, int *s_scan)
     }
 }
 
-// lds_bytes: LDS free for the compaction (0: none)
-template <int B, bool kPos>
+// lds_bytes: LDS free for the compaction (0: none).  kApart: kIdsInMemory is
+// compiled in; its condition is hidden from the optimiser, which otherwise
+// keeps parts of it live through the tracking stages (one event of 4,000 hits
+// 2 % slower).
+template <int B, bool kPos, bool kApart = kPos>
 __device__ __forceinline__ void stage_compact(const Ev &v0, int *s_scan, int lds_bytes)
 {
     const Ev v = fresh(v0);
-    if (compact_fits_lds(v.N, lds_bytes, kPos)) compact_lds<B, kPos>(v, s_scan, lds_bytes);
+    const Compact want = compact_form(v.N, lds_bytes, kPos);
+    const Compact form = kApart ? (Compact)opq((int)want) : want;
+    if (form == Compact::kWhole) compact_lds<B, kPos, kPos>(v, s_scan, lds_bytes);
+    else if (kApart && form == Compact::kIdsInMemory) compact_lds<B, kPos, false>(v, s_scan, lds_bytes);
     else compact_mem<B, kPos>(v, s_scan);
 }
 

@@ -44,3 +44,18 @@ def test_grouped_events_fit_the_launch_bounds(tmp_path):
     _holds(tmp_path, "", [f"max_block_lanes<64, {cap}>() / 64 == 16 || "
                           f"(max_block_lanes<64, {cap}>() / 64 + 1) * event_region_bytes<64>({cap}, 0) > kMaxDynLds"
                           for cap in (0,) + SLOTS])
+
+
+def test_compaction_reach_of_events_tracked_in_lds(tmp_path):
+    """An event that the LDS form tracks names its hits by position, and its
+    compaction still runs in LDS wherever links and tracks alone fit: in the
+    plain form's 64 KiB and in each instance's LDS (26 full modules, at most
+    16,384 hits)."""
+    cases = [(65536, n) for n in (13900, 14100, 16384, 24400)]
+    fits = [f"compact_form({n}, {lds}, true) != Compact::kMemory" for lds, n in cases]
+    for cap in SLOTS:
+        n, lds = min(26 * cap, 16384), f"(int)lds_bytes({cap}, 16384)"
+        fits.append(f"compact_form({n}, {lds}, true) != Compact::kMemory || compact_form({n}, {lds}, false) == Compact::kMemory")
+    _holds(tmp_path, "", fits + ["compact_form(13900, 65536, true) == Compact::kWhole",
+                                 "compact_form(24700, 65536, true) == Compact::kMemory",
+                                 "compact_form(24400, 65536, false) == Compact::kWhole"])

@@ -302,3 +302,14 @@ def test_more_tracks_than_lanes(lanes, tuning, n):
         assert _peak_bound(b, e, *want, misses=1) > lanes
     assert np.diff(want[0]).min() > 10      # tracks, and with them flags, before the noise
     _check(ev, mz[0], tuning, form="batched" if tuning else "plain", **over)
+
+
+@pytest.mark.parametrize("tuning,n", [(None, 539), (None, 545), (None, 630), ((512, 2, 672), 576), ((512, 2, 672), 578),
+                                      ((512, 3, 448), 420), ((512, 3, 448), 430), ((256, 5, 256), 240), ((256, 5, 256), 256),
+                                      ((1024, 1, 1536), 1325), ((1024, 1, 1536), 1400)])
+def test_compaction_with_the_ids_in_lds_and_in_memory(tuning, n):
+    """Events of 26 modules around the hits that leave no room for the ids in
+    the LDS of the compaction (None: the plain form)."""
+    rng = np.random.default_rng(n)
+    ev, mz = zip(*[_event(rng, [n] * 26, t) for t in (n, n // 3)])
+    _check(ev, mz[0], tuning, form="batched" if tuning else "plain")

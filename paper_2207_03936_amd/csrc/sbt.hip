@@ -379,17 +379,11 @@ __global__ __launch_bounds__(kWriteThreads) void k_write_events(HitsArgs H, Work
     }
 }
 
-// Consolidation: one workgroup per event, one lane per track.  The lane
-// copies the coordinates of its track's hits in track order, then fits
-// x(z) and y(z) by unweighted least squares: means, sums centred on the
-// means, residuals, each accumulated over the hits in track order (binary32,
-// no contraction, correctly rounded division).  A track of up to
-// kConsRegHits hits is loaded into registers at once (every load in flight
-// together); a longer one is read again from the inputs for each pass.
-// Batches of dense events only (see k_consolidate_lds).
-constexpr int kConsThreads = 256;
-constexpr int kConsRegHits = 32;
-
+// Consolidation: one lane per track.  The lane copies the coordinates of its
+// track's hits in track order, then fits x(z) and y(z) by unweighted least
+// squares: means, sums centred on the means, residuals, each accumulated over
+// the hits in track order (binary32, no contraction, correctly rounded
+// division).
 __device__ __forceinline__ void write_state(float *__restrict__ state, int t, float xm, float ym, float zm, float tx,
                                             float ty, float c2, int n)
 {
@@ -402,132 +396,7 @@ __device__ __forceinline__ void write_state(float *__restrict__ state, int t, fl
     st[5] = c2 / (float)(2 * n - 4);
 }
 
-__global__ __launch_bounds__(kConsThreads) void k_consolidate(HitsArgs H, const int32_t *__restrict__ eto,
-                                                              const int32_t *__restrict__ tho,
-                                                              const int32_t *__restrict__ th,
-                                                              float *__restrict__ px, float *__restrict__ py,
-                                                              float *__restrict__ pz, float *__restrict__ state)
-{
-    const float *__restrict__ X = H.x;
-    const float *__restrict__ Y = H.y;
-    const float *__restrict__ Z = H.z;
-    for (int e = blockIdx.x; e < H.n_events; e += gridDim.x) {
-        const int hb = H.eo[e];
-        const int t1 = eto[e + 1];
-        for (int t = eto[e] + (int)threadIdx.x; t < t1; t += kConsThreads) {
-            const int lo = tho[t], hi = tho[t + 1];
-            const int n = hi - lo;
-            const float fn = (float)n;
-            if (n <= kConsRegHits) {
-                int id[kConsRegHits];
-                float xs[kConsRegHits], ys[kConsRegHits], zs[kConsRegHits];
-#pragma unroll
-                for (int j = 0; j < kConsRegHits; ++j)
-                    if (j < n) id[j] = hb + th[lo + j];
-#pragma unroll
-                for (int j = 0; j < kConsRegHits; ++j)
-                    if (j < n) {
-                        xs[j] = X[id[j]];
-                        ys[j] = Y[id[j]];
-                        zs[j] = Z[id[j]];
-                    }
-                float sx = 0.0f, sy = 0.0f, sz = 0.0f;
-#pragma unroll
-                for (int j = 0; j < kConsRegHits; ++j)
-                    if (j < n) {
-                        px[lo + j] = xs[j];
-                        py[lo + j] = ys[j];
-                        pz[lo + j] = zs[j];
-                        sx = sx + xs[j];
-                        sy = sy + ys[j];
-                        sz = sz + zs[j];
-                    }
-                const float xm = sx / fn, ym = sy / fn, zm = sz / fn;
-                float szz = 0.0f, sxz = 0.0f, syz = 0.0f;
-#pragma unroll
-                for (int j = 0; j < kConsRegHits; ++j)
-                    if (j < n) {
-                        const float dz = zs[j] - zm;
-                        szz = szz + dz * dz;
-                        sxz = sxz + dz * (xs[j] - xm);
-                        syz = syz + dz * (ys[j] - ym);
-                    }
-                const float tx = sxz / szz, ty = syz / szz;
-                float c2 = 0.0f;
-#pragma unroll
-                for (int j = 0; j < kConsRegHits; ++j)
-                    if (j < n) {
-                        const float dz = zs[j] - zm;
-                        const float rx = xs[j] - (xm + tx * dz);
-                        const float ry = ys[j] - (ym + ty * dz);
-                        c2 = c2 + ((rx * rx) + (ry * ry));
-                    }
-                write_state(state, t, xm, ym, zm, tx, ty, c2, n);
-                continue;
-            }
-            float sx = 0.0f, sy = 0.0f, sz = 0.0f;
-            for (int k = lo; k < hi; ++k) {
-                const int i = hb + th[k];
-                const float x = X[i], y = Y[i], z = Z[i];
-                px[k] = x;
-                py[k] = y;
-                pz[k] = z;
-                sx = sx + x;
-                sy = sy + y;
-                sz = sz + z;
-            }
-            const float xm = sx / fn, ym = sy / fn, zm = sz / fn;
-            float szz = 0.0f, sxz = 0.0f, syz = 0.0f;
-            for (int k = lo; k < hi; ++k) {
-                const int i = hb + th[k];
-                const float dz = Z[i] - zm;
-                szz = szz + dz * dz;
-                sxz = sxz + dz * (X[i] - xm);
-                syz = syz + dz * (Y[i] - ym);
-            }
-            const float tx = sxz / szz, ty = syz / szz;
-            float c2 = 0.0f;
-            for (int k = lo; k < hi; ++k) {
-                const int i = hb + th[k];
-                const float dz = Z[i] - zm;
-                const float rx = X[i] - (xm + tx * dz);
-                const float ry = Y[i] - (ym + ty * dz);
-                c2 = c2 + ((rx * rx) + (ry * ry));
-            }
-            write_state(state, t, xm, ym, zm, tx, ty, c2, n);
-        }
-    }
-}
-
-// Consolidation of events whose coordinates fit the LDS: one workgroup per
-// event.  Lanes that hold consecutive hits of a track, or the j-th hits of
-// neighbouring tracks, gather from lines all over the event, and the events in
-// flight do not fit the L2s (39 KB an event of 3,300 hits): read that way a
-// batch moves several times its bytes, and the packed arrays written a hit
-// per lane go out as single words.  Here an event's coordinates are read once
-// and as they lie into LDS, with its tracks' hit ids (14 B a hit), packed from
-// there in whole lines, and fitted from there, a lane per track.  An event
-// beyond cap gathers from memory.
-//
-// Which kernel, by the batch's mean event (microseconds a call, LDS form
-// against k_consolidate, truth tracks): an event cannot be split, so its
-// coordinates take the whole LDS of a CU (1,024 lanes, 11,600 hits: mu = 7.6 x
-// 1,000 51 / 76, x 100 12 / 26, mu in U{1..25} x 2,000 131 / 254; the 512-lane
-// form with half of it, which sends one mu = 7.6 event in twelve to memory,
-// 66) or, where they average kConsSmallMean hits, a quarter of it (256 lanes,
-// 2,900 hits: low pileup x 2,000 30 / 56 and 63 with the whole, 430 hits x 2,000
-// 18 / 25).  Batches of more than kConsDirectMean hits an event are mostly
-// beyond the LDS and stay with k_consolidate (mu = 30 x 200: 98 / 86).
-// What bounds the mu = 7.6 x 1,000 batch now is the chain of an event (offsets,
-// track offsets, ids, coordinates, fit) at one event per CU, 18 us being the
-// time of its 85 MB at the rate of a large copy.
-constexpr int kConsHits = 11600, kConsHitsSmall = 2900;
-constexpr int kConsSmallMean = 1300, kConsDirectMean = 9000;
-constexpr int kConsBatch = 4;     // hits of a track whose LDS loads are in flight together
-constexpr int kConsDirect = 16;   // the same from memory
-
-// Fit of a track of n hits (see k_consolidate); each(f) calls f on its hits in
-// track order.
+// Fit of a track of n hits; each(f) calls f on its hits in track order.
 template <class Each>
 __device__ __forceinline__ void fit_track(float *__restrict__ state, int t, int n, Each &&each)
 {
@@ -557,94 +426,183 @@ __device__ __forceinline__ void fit_track(float *__restrict__ state, int t, int 
     write_state(state, t, xm, ym, zm, tx, ty, c2, n);
 }
 
+// an event's hits and tracks: its first hit, hits, tracks [t0, t1), the first
+// of their hits and the number of them
+struct ConsEvent {
+    int hb, N, t0, t1, lo0, nh;
+};
+
+constexpr int kConsBatch = 4;   // hits of a track whose LDS loads are in flight together
+constexpr int kConsColumn = 8;  // hits of a lane packed together from a column
+constexpr int kConsKeep = 16;   // hits of a track kept in registers for the fit
+
+// An event whose coordinates and ids fit the LDS (cap hits, 14 B each): read
+// once and as they lie, packed and fitted from there.
 template <int B>
-__global__ __launch_bounds__(B) void k_consolidate_lds(HitsArgs H, const int32_t *__restrict__ eto,
-                                                       const int32_t *__restrict__ tho,
-                                                       const int32_t *__restrict__ th, float *__restrict__ px,
-                                                       float *__restrict__ py, float *__restrict__ pz,
-                                                       float *__restrict__ state, int cap)
+__device__ __forceinline__ void cons_whole(const HitsArgs &H, const ConsEvent &v, const int32_t *__restrict__ tho,
+                                           const int32_t *__restrict__ th, float *__restrict__ px,
+                                           float *__restrict__ py, float *__restrict__ pz, float *__restrict__ state,
+                                           int cap)
 {
     float *lx = reinterpret_cast<float *>(g_lds), *ly = lx + cap, *lz = ly + cap;
     uint16_t *lid = reinterpret_cast<uint16_t *>(lz + cap);
     const int tid = (int)threadIdx.x;
-    for (int e = blockIdx.x; e < H.n_events; e += gridDim.x) {
-        const int hb = H.eo[e], N = H.eo[e + 1] - hb;
-        const int t0 = eto[e], t1 = eto[e + 1];
-        if (t0 >= t1) continue;
-        const int lo0 = tho[t0], nh = tho[t1] - lo0;
-        const float *__restrict__ X = H.x + hb;
-        const float *__restrict__ Y = H.y + hb;
-        const float *__restrict__ Z = H.z + hb;
-        if (N <= cap && nh <= cap) {
+    const float *__restrict__ X = H.x + v.hb;
+    const float *__restrict__ Y = H.y + v.hb;
+    const float *__restrict__ Z = H.z + v.hb;
 #pragma unroll 4
-            for (int i = tid; i < N; i += B) {
-                lx[i] = X[i];
-                ly[i] = Y[i];
-                lz[i] = Z[i];
-            }
+    for (int i = tid; i < v.N; i += B) {
+        lx[i] = X[i];
+        ly[i] = Y[i];
+        lz[i] = Z[i];
+    }
 #pragma unroll 4
-            for (int k = tid; k < nh; k += B) lid[k] = (uint16_t)th[lo0 + k];
-            __syncthreads();
-            for (int k = tid; k < nh; k += B) {
-                const int i = lid[k];
-                px[lo0 + k] = lx[i];
-                py[lo0 + k] = ly[i];
-                pz[lo0 + k] = lz[i];
-            }
-            for (int t = t0 + tid; t < t1; t += B) {
-                const int l = tho[t] - lo0;
-                const int n = tho[t + 1] - lo0 - l;
-                fit_track(state, t, n, [&](auto &&f) {
-                    for (int j0 = 0; j0 < n; j0 += kConsBatch) {
-                        float3 h[kConsBatch];
+    for (int k = tid; k < v.nh; k += B) lid[k] = (uint16_t)th[v.lo0 + k];
+    __syncthreads();
+    for (int k = tid; k < v.nh; k += B) {
+        const int i = lid[k];
+        px[v.lo0 + k] = lx[i];
+        py[v.lo0 + k] = ly[i];
+        pz[v.lo0 + k] = lz[i];
+    }
+    for (int t = v.t0 + tid; t < v.t1; t += B) {
+        const int l = tho[t] - v.lo0;
+        const int n = tho[t + 1] - v.lo0 - l;
+        fit_track(state, t, n, [&](auto &&f) {
+            for (int j0 = 0; j0 < n; j0 += kConsBatch) {
+                float3 h[kConsBatch];
 #pragma unroll
-                        for (int u = 0; u < kConsBatch; ++u) {
-                            const int i = lid[l + min(j0 + u, n - 1)];
-                            h[u] = make_float3(lx[i], ly[i], lz[i]);
-                        }
-#pragma unroll
-                        for (int u = 0; u < kConsBatch; ++u)
-                            if (j0 + u < n) f(h[u]);
-                    }
-                });
-            }
-            __syncthreads();
-        } else {
-            for (int t = t0 + tid; t < t1; t += B) {
-                const int lo = tho[t], n = tho[t + 1] - lo;
-                // up to kConsDirect hits of the track in flight together, and
-                // kept for the fit where they are all of it
-                float3 h[kConsDirect];
-                for (int j0 = 0; j0 < n; j0 += kConsDirect) {
-                    int i[kConsDirect];
-#pragma unroll
-                    for (int u = 0; u < kConsDirect; ++u) i[u] = th[lo + min(j0 + u, n - 1)];
-#pragma unroll
-                    for (int u = 0; u < kConsDirect; ++u) h[u] = make_float3(X[i[u]], Y[i[u]], Z[i[u]]);
-#pragma unroll
-                    for (int u = 0; u < kConsDirect; ++u)
-                        if (j0 + u < n) {
-                            px[lo + j0 + u] = h[u].x;
-                            py[lo + j0 + u] = h[u].y;
-                            pz[lo + j0 + u] = h[u].z;
-                        }
+                for (int u = 0; u < kConsBatch; ++u) {
+                    const int i = lid[l + min(j0 + u, n - 1)];
+                    h[u] = make_float3(lx[i], ly[i], lz[i]);
                 }
-                if (n <= kConsDirect) {
-                    fit_track(state, t, n, [&](auto &&f) {
 #pragma unroll
-                        for (int u = 0; u < kConsDirect; ++u)
-                            if (u < n) f(h[u]);
-                    });
-                } else {
-                    fit_track(state, t, n, [&](auto &&f) {
-                        for (int j = 0; j < n; ++j) {
-                            const int i = th[lo + j];
-                            f(make_float3(X[i], Y[i], Z[i]));
-                        }
-                    });
-                }
+                for (int u = 0; u < kConsBatch; ++u)
+                    if (j0 + u < n) f(h[u]);
             }
+        });
+    }
+    __syncthreads();
+}
+
+// A larger event: one coordinate of room hits at a time through the LDS and
+// packed from there.  The fit gathers from the inputs again (the packed arrays
+// are outputs, perhaps in host memory, and never read).
+template <int B>
+__device__ __forceinline__ void cons_columns(const HitsArgs &H, const ConsEvent &v, const int32_t *__restrict__ tho,
+                                             const int32_t *__restrict__ th, float *__restrict__ px,
+                                             float *__restrict__ py, float *__restrict__ pz,
+                                             float *__restrict__ state, int room)
+{
+    float *l = reinterpret_cast<float *>(g_lds);
+    const int tid = (int)threadIdx.x;
+    const int32_t *__restrict__ ids = th + v.lo0;
+#pragma unroll 1
+    for (int c = 0; c < 3; ++c) {
+        const float *__restrict__ src = (c == 0 ? H.x : c == 1 ? H.y : H.z) + v.hb;
+        float *__restrict__ dst = (c == 0 ? px : c == 1 ? py : pz) + v.lo0;
+#pragma unroll 1
+        for (int i0 = 0; i0 < v.N; i0 += room) {
+            const int m = min(room, v.N - i0);
+#pragma unroll 8
+            for (int i = tid; i < m; i += B) l[i] = src[i0 + i];
+            __syncthreads();
+            for (int k = tid; k < v.nh; k += kConsColumn * B) {
+                unsigned id[kConsColumn];
+#pragma unroll
+                for (int u = 0; u < kConsColumn; ++u) id[u] = (unsigned)(ids[min(k + u * B, v.nh - 1)] - i0);
+                float f[kConsColumn];
+#pragma unroll
+                for (int u = 0; u < kConsColumn; ++u) f[u] = l[min(id[u], (unsigned)(m - 1))];
+#pragma unroll
+                for (int u = 0; u < kConsColumn; ++u)
+                    if (k + u * B < v.nh && id[u] < (unsigned)m) dst[k + u * B] = f[u];
+            }
+            __syncthreads();
         }
+    }
+    const float *__restrict__ X = H.x + v.hb;
+    const float *__restrict__ Y = H.y + v.hb;
+    const float *__restrict__ Z = H.z + v.hb;
+    for (int t = v.t0 + tid; t < v.t1; t += B) {
+        const int l0 = tho[t] - v.lo0, n = tho[t + 1] - v.lo0 - l0;
+        float3 h[kConsKeep];
+        int id[kConsKeep];
+#pragma unroll
+        for (int j = 0; j < kConsKeep; ++j)
+            if (j < n) id[j] = ids[l0 + j];
+#pragma unroll
+        for (int j = 0; j < kConsKeep; ++j)
+            if (j < n) h[j] = make_float3(X[id[j]], Y[id[j]], Z[id[j]]);
+        fit_track(state, t, n, [&](auto &&f) {
+#pragma unroll
+            for (int j = 0; j < kConsKeep; ++j)
+                if (j < n) f(h[j]);
+            for (int j0 = kConsKeep; j0 < n; j0 += kConsBatch) {
+                float3 g[kConsBatch];
+#pragma unroll
+                for (int u = 0; u < kConsBatch; ++u) {
+                    const int i = ids[l0 + min(j0 + u, n - 1)];
+                    g[u] = make_float3(X[i], Y[i], Z[i]);
+                }
+#pragma unroll
+                for (int u = 0; u < kConsBatch; ++u)
+                    if (j0 + u < n) f(g[u]);
+            }
+        });
+    }
+}
+
+// Gathered a lane per track from memory, an event's coordinates come from lines
+// all over it, and the events in flight do not fit the L2s (39 KB an event of
+// 3,300 hits): a batch moves several times its bytes, and the packed arrays go
+// out as single words.  So both forms read an event's coordinates as they lie
+// into LDS and write the packed arrays from there in whole lines.  A workgroup
+// per event, in three sizes: the whole LDS of a CU (1,024 lanes), half of it
+// (512) or a quarter (256), and in each the columns for what is larger.
+//
+// The host knows only the batch's mean event, and any form has to do with any
+// event.  With a plain gather behind the whole form, 500 events of 5,100 hits
+// among 2,000 empty ones took 105 us, and 50 of 8,600 among 1,000 of 420 67,
+// where a gather of the whole batch took 68 and 44; with the columns they take
+// 56 and 42, and batches of large events gain too (mu = 30 x 400 159 -> 108).
+// Lines (us, both sides; truth tracks):
+//  - Up to 256 events (the CUs of the device), or 768 of more than 2,300 hits:
+//    1,024 lanes, as the largest event decides (mu = 7.6 x 600 31, 35 with 512; x 800 38, 37; x
+//    1,000 49, 47).
+//  - Mean events of up to 2,300 hits: 256 lanes (2,000 events of 2,170 hits
+//    44, 53 with 512; of 2,610 61, 58).
+//  - Up to 5,100: 512 lanes (2,000 events of 4,910 hits 86, 106 with 1,024; of
+//    5,660 137, 118).
+//  - Larger ones: 1,024 lanes (mu in U{1..25} x 1,000 76, 107 with 512; mu = 30
+//    x 400 108, 120; 30,000 hits x 300 276, 361).
+// Where few of a batch's events hold most of its work a form may be too narrow
+// for them (20 of 13,000 hits among 980 of 420: 84 us, a gather 66), and where
+// most hits lie in events without tracks too wide for the rest (300 such of
+// 10,000 hits and 700 of 420: 14 us, a gather 12).
+// What bounds it is the chain of an event (offsets, track offsets, ids,
+// coordinates, fit) at four, two or one event per CU: mu = 7.6 x 1,000 moves
+// its 85 MB in 18 us at the rate of a large copy.
+constexpr int kConsHits1024 = 11600, kConsHits512 = 5800, kConsHits256 = 2900;   // whole events
+constexpr int kConsMean256 = 2300, kConsMean512 = 5100;
+constexpr int kConsFew = 256;
+
+template <int B>
+__global__ __launch_bounds__(B) void k_consolidate(
+    HitsArgs H, const int32_t *__restrict__ eto, const int32_t *__restrict__ tho, const int32_t *__restrict__ th,
+    float *__restrict__ px, float *__restrict__ py, float *__restrict__ pz, float *__restrict__ state, int cap)
+{
+    for (int e = blockIdx.x; e < H.n_events; e += gridDim.x) {
+        ConsEvent v;
+        v.hb = H.eo[e];
+        v.N = H.eo[e + 1] - v.hb;
+        v.t0 = eto[e];
+        v.t1 = eto[e + 1];
+        if (v.t0 >= v.t1) continue;
+        v.lo0 = tho[v.t0];
+        v.nh = tho[v.t1] - v.lo0;
+        if (__builtin_expect(v.N <= cap && v.nh <= cap, 1)) cons_whole<B>(H, v, tho, th, px, py, pz, state, cap);
+        else cons_columns<B>(H, v, tho, th, px, py, pz, state, 14 * cap / 4);
     }
 }
 
@@ -1186,19 +1144,19 @@ int sbt_consolidate(const sbt_hits *hits, const sbt_tracks *tracks, sbt_track_st
     const HitsArgs H = hits_args(hits);
     const dim3 grid(std::min(H.n_events, 8192));
     const hipStream_t st = (hipStream_t)stream;
-    const int32_t *eto = tracks->event_track_offsets, *tho = tracks->track_hit_offsets, *th = tracks->track_hits;
     const long long mean = H.n_hits / H.n_events;
-    if (mean > kConsDirectMean) {
-        hipLaunchKernelGGL(k_consolidate, grid, dim3(kConsThreads), 0, st, H, eto, tho, th, out->hit_x, out->hit_y,
-                           out->hit_z, out->state);
-    } else if (mean > kConsSmallMean) {
-        if ((rc = allow_lds(reinterpret_cast<const void *>(k_consolidate_lds<1024>), 14 * kConsHits))) return rc;
-        hipLaunchKernelGGL(k_consolidate_lds<1024>, grid, dim3(1024), 14 * kConsHits, st, H, eto, tho, th, out->hit_x,
-                           out->hit_y, out->hit_z, out->state, kConsHits);
-    } else {
-        hipLaunchKernelGGL(k_consolidate_lds<256>, grid, dim3(256), 14 * kConsHitsSmall, st, H, eto, tho, th,
-                           out->hit_x, out->hit_y, out->hit_z, out->state, kConsHitsSmall);
-    }
+    auto launch = [&](auto kernel, int lanes, int cap) -> int {
+        if (int r = allow_lds(reinterpret_cast<const void *>(kernel), 14 * (size_t)cap)) return r;
+        hipLaunchKernelGGL(kernel, grid, dim3(lanes), 14 * cap, st, H, tracks->event_track_offsets,
+                           tracks->track_hit_offsets, tracks->track_hits, out->hit_x, out->hit_y, out->hit_z,
+                           out->state, cap);
+        return SBT_OK;
+    };
+    const bool few = H.n_events <= (mean > kConsMean256 ? 3 * kConsFew : kConsFew);
+    if (few || mean > kConsMean512) rc = launch(k_consolidate<1024>, 1024, kConsHits1024);
+    else if (mean > kConsMean256) rc = launch(k_consolidate<512>, 512, kConsHits512);
+    else rc = launch(k_consolidate<256>, 256, kConsHits256);
+    if (rc) return rc;
     return hipGetLastError() == hipSuccess ? SBT_OK : SBT_ERR_HIP;
 }
 

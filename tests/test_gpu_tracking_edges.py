@@ -313,3 +313,60 @@ def test_compaction_with_the_ids_in_lds_and_in_memory(tuning, n):
     rng = np.random.default_rng(n)
     ev, mz = zip(*[_event(rng, [n] * 26, t) for t in (n, n // 3)])
     _check(ev, mz[0], tuning, form="batched" if tuning else "plain")
+
+
+def _random_tracks(rng, n, longest):
+    """Disjoint tracks over a random choice of n hits, as (lengths, hit ids)."""
+    ids = rng.permutation(n)[:int(0.9 * n)]
+    lengths = []
+    while sum(lengths) + 3 <= ids.size:
+        lengths.append(int(min(ids.size - sum(lengths), rng.choice([3, 4, 11, 16, 17, 26, longest]))))
+    if lengths and lengths[-1] < 3:
+        lengths.pop()
+    return lengths, ids[:sum(lengths)]
+
+
+@pytest.mark.parametrize("pinned", [False, True])
+@pytest.mark.parametrize("fill,sizes", [
+    (0, (3, 2899, 2900, 2901, 5801, 10150, 10151, 11600, 11601)),           # one event per CU: 1,024 lanes
+    (0, (40600, 40601, 65535)),
+    (400, (0, 2900, 2901, 10149, 10150, 10151, 20301, 31000)),              # 256 lanes, one to four columns
+    (5200, (5799, 5800, 5801, 20300, 20301, 41000)),                        # 512 lanes
+    (11000, (100, 11599, 11601, 40601))])                                   # 1,024 lanes by the mean
+def test_consolidation_of_uneven_batches(fill, sizes, pinned):
+    """Events around what each form holds whole, and in one column and several,
+    among many of another size (fill), with tracks of up to 64 hits: packed
+    coordinates and states equal, bit for bit, the same binary32 operations
+    done in numpy (no tolerance); into device and into pinned host memory."""
+    import torch
+    cus = 256
+    rng = np.random.default_rng(fill + len(sizes))
+    n = list(sizes)
+    if fill == 400:
+        n += [int(v) for v in rng.integers(0, 800, cus + 40)]
+    elif fill == 5200:
+        n += [int(v) for v in rng.integers(3, 9000, 3 * cus + 10)]
+    elif fill:
+        n += [fill] * (cus + 7)
+    n = [n[i] for i in rng.permutation(len(n))]
+    eo = np.concatenate([[0], np.cumsum(n)]).astype(np.int32)
+    mean = int(eo[-1]) // len(n)
+    assert {0: len(n) <= cus, 400: len(n) > cus and mean <= 2300, 5200: len(n) > 3 * cus and 2300 < mean <= 5100,
+            11000: len(n) > cus and mean > 5100}[fill]
+    print(f"[gpu] {len(n)} events of {mean} hits, pinned {pinned}", flush=True)
+    x, y, z = (rng.normal(0, s, eo[-1]).astype(np.float32) for s in (20, 20, 300))
+    per = [_random_tracks(rng, v, 64) for v in n]
+    th = np.concatenate([p[1] for p in per]).astype(np.int32)
+    tho = np.concatenate([[0], np.cumsum(np.concatenate([p[0] for p in per]))]).astype(np.int32)
+    eto = np.concatenate([[0], np.cumsum([len(p[0]) for p in per])]).astype(np.int32)
+    g = np.concatenate([eo[e] + per[e][1] for e in range(len(n))])
+    b = synth.Batch(x=x, y=y, z=z, event_offsets=eo, module_offsets=np.repeat(eo, 3)[:3 * len(n) + 1].astype(np.int32),
+                    module_z=np.arange(3, dtype=np.float32), truth=np.zeros(0, np.int32))
+    dev, out = sbt.DeviceBatch(b), sbt.DeviceTracks(b.n_events, b.n_hits)
+    for dst, src in zip((out.eto, out.tho, out.th), (eto, tho, th)):
+        dst[:len(src)] = torch.from_numpy(src).to(dst.device)
+    want = (x[g], y[g], z[g], _fit32(x[g], y[g], z[g], tho))
+    got = sbt.sbt_consolidate(dev, out, sbt.TrackStates(b.n_hits, pinned=pinned))
+    torch.cuda.synchronize()
+    for a, w in zip(got.to_host(len(tho) - 1, len(th)), want):
+        assert np.array_equal(np.asarray(a).view(np.uint32), np.ascontiguousarray(w).view(np.uint32))

@@ -180,7 +180,10 @@ typedef struct sbt_tracks {
  *                     hold the phi-sorted hits of consecutive modules
  *                     (0..2048), rounded down to a compiled one (0, 256,
  *                     448, 672, 768, 1024, 1536); an event with a larger
- *                     module reads all its modules from memory.
+ *                     module reads all its modules from memory.  (Three or
+ *                     more 512-lane workgroups per CU given 448 run 480-hit
+ *                     slots where their LDS still fits three times: fewer
+ *                     events exceed them, and none that fit 448.)
  * lds_owner_hits      events with at most this many hits keep their hit
  *                     flags (one bit per hit) in LDS, larger ones in
  *                     memory (0..65536).  One 1,024-lane workgroup per CU
@@ -316,7 +319,9 @@ int sbt_autotune(sbt_context *ctx, const sbt_hits *sample, sbt_tracks *tracks, v
 
 /* Stage timing of the last call on this context, in milliseconds, measured
  * with HIP events on the call's stream when profiling is on (graphs are then
- * bypassed).  stage_ms[0] = persistent kernel, [1] = scan, [2] = CSR write.
+ * bypassed).  stage_ms[0] = event order and persistent kernels, [1] = scan,
+ * [2] = CSR write.  Batches of up to 4,096 events scan and write in one
+ * kernel: its time is [2], and [1] only the gap between two events.
  * Synchronises on the events.                                             */
 int sbt_context_set_profiling(sbt_context *ctx, int32_t on);
 int sbt_context_stage_ms(sbt_context *ctx, float *stage_ms, int32_t n);

@@ -318,8 +318,10 @@ __global__ __launch_bounds__(kWriteThreads) void k_write(HitsArgs H, Work W, Out
 // few loads a lane, all in flight.  It saves a launch and k_scan's single
 // workgroup, and reads E * E / 2 counts instead of E: mu = 7.6 x 1,000 takes
 // 284 us instead of 290, 2,048 events of about 1,260 hits 239 instead of
-// 246, 4,000 of them 409 instead of 416, and as the reads grow with the
-// square and the saving is constant, longer batches keep the two kernels.
+// 246, 4,000 of them 409 instead of 416.  The reads grow with the square and
+// the saving does not, so there is a length where the two kernels are better;
+// it lies beyond 4,096 events, where a lane's sixteen counts end and with them
+// this kernel.
 constexpr int kScanInWrite = 16 * kWriteThreads;
 __global__ __launch_bounds__(kWriteThreads) void k_scan_write(HitsArgs H, Work W, OutArgs O)
 {
@@ -1240,7 +1242,10 @@ sbt_tuning default_tuning()
 //  - One event of at most 4,500 hits: 512 lanes, 1,024-hit slots.  Its steps'
 //    work fits eight waves, and barriers and scans over eight cost less than
 //    over sixteen (2,614 hits: 104, 110; 3,500: 121, 126; 4,510: 136, 136; with
-//    two workgroups' 768-hit slots 6,046: 156, 145).
+//    two workgroups' 768-hit slots 6,046: 156, 145).  Several alike gain the
+//    same (32 of up to 2,757 hits: 114, 123), but of several only the mean is
+//    known and the largest decides (256 of 2,700 on average and up to 10,900:
+//    234, 201), so the rule stops at one.
 //  - Larger batches: 512 lanes, two workgroups per CU with 672-hit slots;
 //    batches of large events with 768-hit slots (the largest of which two fit a
 //    CU), so that their busiest modules stay in LDS (mu in U{1..25} x 1,000:

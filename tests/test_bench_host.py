@@ -95,3 +95,10 @@ def test_committed_summaries_describe_the_committed_kernels():
     for name in ("k_persistent_mu7.6_x1000_traffic.json", "k_persistent_mu7.6_x1000_sq.json"):
         with open(os.path.join(ROOT, "profiles", name)) as f:
             assert json.load(f)["kernel_source_hash"] == h, name
+
+
+def test_stage_times_carry_the_names_of_the_kernels_that_ran():
+    """Up to 4,096 events the scan and the CSR write are one kernel, timed in
+    the third stage; beyond, one each."""
+    assert bench.stage_entry([0.25, 0.005, 0.008], 4096) == {"k_persistent": 0.25, "k_scan_write": 0.008}
+    assert bench.stage_entry([3.2, 0.036, 0.077], 4097) == {"k_persistent": 3.2, "k_scan": 0.036, "k_write": 0.077}

@@ -1237,8 +1237,8 @@ sbt_tuning default_tuning()
 //  - At most one event per compute unit, or at most two large ones (4,000 hits
 //    or more on average): 1,024 lanes per event, one workgroup per CU with
 //    1,536-hit slots.  The batch takes as long as its largest event, and there
-//    are too few events to fill the device twice (mu in U{1..25} x 256: 210,
-//    251 with 512 lanes x 2 per CU; x 1,000: 586, 383).
+//    are too few events to fill the device twice (mu in U{1..25} x 256: 206,
+//    250 with 512 lanes x 2 per CU; x 1,000: 583, 377).
 //  - One event of at most 4,500 hits: 512 lanes, 1,024-hit slots.  Its steps'
 //    work fits eight waves, and barriers and scans over eight cost less than
 //    over sixteen (2,614 hits: 104, 110; 3,500: 121, 126; 4,510: 136, 136; with
@@ -1249,25 +1249,25 @@ sbt_tuning default_tuning()
 //  - Larger batches: 512 lanes, two workgroups per CU with 672-hit slots;
 //    batches of large events with 768-hit slots (the largest of which two fit a
 //    CU), so that their busiest modules stay in LDS (mu in U{1..25} x 1,000:
-//    383, 721).
+//    377, 707).
 //  - From 8.5 mid-size events per CU on: 512 lanes, three per CU with 448-hit
 //    slots (launched with 480; the instance held to six waves per SIMD).  The few events with a
 //    larger module run from memory at about three times the time, which a long
-//    batch hides (mu = 7.6 x 2,300: 590, 625; x 4,000: 819, 1,044) and a
-//    shorter one does not (x 2,000: 574, 534; x 1,000: 515, 274).
+//    batch hides (mu = 7.6 x 2,300: 589, 610; x 4,000: 811, 1,040) and a
+//    shorter one does not (x 2,000: 574, 520; x 1,000: 511, 270).
 //  - From fifteen large events per CU on: the same in two passes.  The events
 //    whose busiest module exceeds the slots (38 % of mu in U{1..25} exceed 448
 //    hits) are set aside and then run with 768-hit slots, two per CU
-//    (x 10,000: 3,387, 3,575 in one pass with 768-hit slots; x 4,000: 1,442,
-//    1,484).
+//    (x 10,000: 3,387, 3,575 in one pass with 768-hit slots; x 4,000: 1,413,
+//    1,459).
 //  - Very large events (9,000 hits or more on average) have modules beyond the
 //    768-hit slots: 1,024 lanes with 1,536-hit slots whatever their number
-//    (mu = 30 x 1,000: 1,040, 2,680).
+//    (mu = 30 x 400: 467, 1,331).
 //  - Small events (2,500 hits or fewer on average), whose modules fit 256-hit
 //    slots: 256 lanes, five workgroups per CU, when there are more than two
 //    per CU (800 events of about 1,260 hits: 143, 205 with 512 lanes x 2;
-//    2,000: 238, 393), and 512 lanes with 448-hit slots when there are fewer
-//    (one of 500 hits: 70, 81 with 1,024 lanes).
+//    2,000 of 1,330: 224, 389), and 512 lanes with 448-hit slots when there
+//    are fewer (512 of 1,330: 119, 130 with 256 lanes).
 sbt_tuning size_tuning(int E, int H, int cus)
 {
     sbt_tuning t = default_tuning();

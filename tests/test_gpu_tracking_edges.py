@@ -331,6 +331,7 @@ def _random_tracks(rng, n, longest):
     (0, (3, 2899, 2900, 2901, 5801, 10150, 10151, 11600, 11601)),           # one event per CU: 1,024 lanes
     (0, (40600, 40601, 65535)),
     (400, (0, 2900, 2901, 10149, 10150, 10151, 20301, 31000)),              # 256 lanes, one to four columns
+    (30, (2901, 10151)),                                                    # more events than workgroups
     (5200, (5799, 5800, 5801, 20300, 20301, 41000)),                        # 512 lanes
     (11000, (100, 11599, 11601, 40601))])                                   # 1,024 lanes by the mean
 def test_consolidation_of_uneven_batches(fill, sizes, pinned):
@@ -344,6 +345,8 @@ def test_consolidation_of_uneven_batches(fill, sizes, pinned):
     n = list(sizes)
     if fill == 400:
         n += [int(v) for v in rng.integers(0, 800, cus + 40)]
+    elif fill == 30:
+        n += [int(v) for v in rng.integers(0, 60, 9000)]
     elif fill == 5200:
         n += [int(v) for v in rng.integers(3, 9000, 3 * cus + 10)]
     elif fill:
@@ -351,7 +354,7 @@ def test_consolidation_of_uneven_batches(fill, sizes, pinned):
     n = [n[i] for i in rng.permutation(len(n))]
     eo = np.concatenate([[0], np.cumsum(n)]).astype(np.int32)
     mean = int(eo[-1]) // len(n)
-    assert {0: len(n) <= cus, 400: len(n) > cus and mean <= 2300, 5200: len(n) > 3 * cus and 2300 < mean <= 5100,
+    assert {0: len(n) <= cus, 30: len(n) > 8192 and mean <= 2300, 400: len(n) > cus and mean <= 2300, 5200: len(n) > 3 * cus and 2300 < mean <= 5100,
             11000: len(n) > cus and mean > 5100}[fill]
     print(f"[gpu] {len(n)} events of {mean} hits, pinned {pinned}", flush=True)
     x, y, z = (rng.normal(0, s, eo[-1]).astype(np.float32) for s in (20, 20, 300))
